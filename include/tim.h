@@ -382,7 +382,8 @@ tim_status tim_run(tim_ctx *ctx, const tim_graph *g, int model, int k, double ep
  * live edges.  d_counts (device uint32[runs], nullable) receives each run's
  * spread, *total (host, nullable) their sum and *mean (host, nullable) the
  * estimate total / runs.  The first call on a graph builds its out-edge lists
- * (8(n+1) + 8m bytes, freed with the graph). */
+ * (8(n+1) + 8m bytes, freed with the graph), the first under IC also their
+ * thresholds (4m bytes; without room for them the runs derive each one). */
 tim_status tim_spread_mc(tim_ctx *ctx, const tim_graph *g, int model, uint64_t seed, uint64_t first, uint64_t runs,
                          const int32_t *seeds, int nseeds, uint32_t *d_counts, double *mean, uint64_t *total);
 

@@ -153,6 +153,7 @@ struct tim_graph {
   int64_t* out_off = nullptr;
   int32_t* out_dst = nullptr;
   uint32_t* out_eid = nullptr;
+  uint32_t* out_thr = nullptr;  // IC threshold of each out-edge, built on the first IC use
 };
 
 namespace {
@@ -2229,6 +2230,7 @@ void tim_graph_free(tim_graph* g) {
   if (g->out_off) (void)hipFree(g->out_off);
   if (g->out_dst) (void)hipFree(g->out_dst);
   if (g->out_eid) (void)hipFree(g->out_eid);
+  if (g->out_thr) (void)hipFree(g->out_thr);
   delete g;
 }
 
@@ -2650,6 +2652,22 @@ tim_status tim_spread_mc(tim_ctx* c, const tim_graph* g, int model, uint64_t see
   a.out_off = gm->out_off;
   a.out_dst = gm->out_dst;
   a.out_eid = gm->out_eid;
+  // IC: the thresholds in out-list order, built by the first such call (without the memory for them the kernel
+  // derives each from the in-lists)
+  struct NewThr {
+    uint32_t* p = nullptr;
+    ~NewThr() {
+      if (p) (void)hipFree(p);
+    }
+  } new_thr;
+  if (model == TIM_MODEL_IC && !gm->out_thr && runs) {
+    if (hipMalloc(&new_thr.p, (size_t)g->m * 4) != hipSuccess) {
+      new_thr.p = nullptr;
+      (void)hipGetLastError();
+    }
+  }
+  a.build_thr = new_thr.p != nullptr;
+  a.out_thr = new_thr.p ? new_thr.p : gm->out_thr;
   a.seed = seed;
   a.first = first;
   a.runs = runs;
@@ -2667,6 +2685,10 @@ tim_status tim_spread_mc(tim_ctx* c, const tim_graph* g, int model, uint64_t see
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipMemcpyAsync(c->ctr_host, c->ctr, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
+  if (new_thr.p) {
+    gm->out_thr = new_thr.p;
+    new_thr.p = nullptr;
+  }
   const uint64_t sum = c->ctr_host[1];
   if (total) *total = sum;
   if (mean) *mean = runs ? (double)sum / (double)runs : 0.0;

@@ -196,6 +196,8 @@ struct SpreadArgs {
   const int64_t* out_off;     // n+1
   const int32_t* out_dst;     // m: head of each out-edge
   const uint32_t* out_eid;    // m: its in-CSR edge id
+  uint32_t* out_thr;          // m: its IC threshold (IC only)
+  int build_thr;              // out_thr is still to be filled (before the runs)
   uint64_t seed, first, runs;
   const int32_t* seeds;       // nseeds node ids (repeats allowed)
   int nseeds;
