@@ -695,23 +695,29 @@ tim_status greedy(tim_ctx* c, int64_t n, uint64_t nsets, const int64_t* set_off,
   if (wb && nsets && (!c->budget || c->held - c->bucket.bytes + wb <= c->budget / 2) &&
       ensure(c, c->bucket, wb, "greedy workspace") == TIM_OK)
     a.bkt = c->bucket.p;
-  if (c->prof_on) HIP_TRY(hipEventRecord(c->pev[0], c->stream));
-  if (index) tim::launch_index(a, c->stream);
-  else tim::launch_counts(a, c->stream);
-  if (c->prof_on) HIP_TRY(hipEventRecord(c->pev[1], c->stream));
-  tim::launch_greedy(a, k, c->stream);
-  if (c->prof_on) HIP_TRY(hipEventRecord(c->pev[2], c->stream));
-  HIP_TRY(hipGetLastError());
+  a.k = k;
   std::vector<unsigned long long> keys((size_t)k);
-  HIP_TRY(hipMemcpyAsync(keys.data(), a.best, (size_t)k * 8, hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(hipStreamSynchronize(c->stream));
-  if (c->prof_on) {
-    float ms_index = 0.f, ms_greedy = 0.f;
-    HIP_TRY(hipEventElapsedTime(&ms_index, c->pev[0], c->pev[1]));
-    HIP_TRY(hipEventElapsedTime(&ms_greedy, c->pev[1], c->pev[2]));
-    c->prof.index_calls += 1;
-    c->prof.index_ms += ms_index;
-    c->prof.greedy_ms += ms_greedy;
+  for (;;) {
+    if (c->prof_on) HIP_TRY(hipEventRecord(c->pev[0], c->stream));
+    if (index) tim::launch_index(a, c->stream);
+    else tim::launch_counts(a, c->stream);
+    if (c->prof_on) HIP_TRY(hipEventRecord(c->pev[1], c->stream));
+    tim::launch_greedy(a, k, c->stream);
+    if (c->prof_on) HIP_TRY(hipEventRecord(c->pev[2], c->stream));
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipMemcpyAsync(keys.data(), a.best, (size_t)k * 8, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    if (c->prof_on) {
+      float ms_index = 0.f, ms_greedy = 0.f;
+      HIP_TRY(hipEventElapsedTime(&ms_index, c->pev[0], c->pev[1]));
+      HIP_TRY(hipEventElapsedTime(&ms_greedy, c->pev[1], c->pev[2]));
+      c->prof.index_calls += 1;
+      c->prof.index_ms += ms_index;
+      c->prof.greedy_ms += ms_greedy;
+    }
+    // a key of 0: the candidates of the largest counts did not decide that step; run it over all nodes
+    if (keys[(size_t)k - 1] != 0ull || a.all_nodes) break;
+    a.all_nodes = 1;
   }
   for (int j = 0; j < k; ++j) {
     seeds[j] = (int32_t)(0xFFFFFFFFull - (keys[j] & 0xFFFFFFFFull));

@@ -35,7 +35,8 @@ __device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long x
   return t;
 }
 
-// Exclusive block scan of 64-bit values (256 threads).
+// Exclusive block scan of 64-bit values (T threads, red[T / 64]).
+template <int T = kThreads>
 __device__ __forceinline__ unsigned long long block_excl_scan(unsigned long long x, unsigned long long* red,
                                                               unsigned long long* total) {
   const int lane = threadIdx.x % 64, wv = threadIdx.x / 64;
@@ -48,7 +49,7 @@ __device__ __forceinline__ unsigned long long block_excl_scan(unsigned long long
   if (lane == 63) red[wv] = incl;
   __syncthreads();
   unsigned long long carry = 0, all = 0;
-  for (int w = 0; w < kThreads / 64; ++w) {
+  for (int w = 0; w < T / 64; ++w) {
     if (w < wv) carry += red[w];
     all += red[w];
   }
@@ -412,6 +413,10 @@ __global__ __launch_bounds__(kThreads) void scatter_kernel(V sets, uint64_t nset
 // 65536-entry chunks, for one more atomic per node present in each extra chunk:
 // the index and greedy run about 7% faster on a 1M-node graph.
 constexpr int kBucketShiftMin = 13, kBucketShiftMax = 13;
+// Collections of at most kDirectCounts entries are counted by the direct pass:
+// the sort's eight launches cost more than its atomics save (0.7M entries: 2%
+// of the 1.5 ms of a TIM+ run on 15K nodes; at 2 to 4M entries the two are even).
+constexpr uint64_t kDirectCounts = 1ull << 20;
 constexpr int kBucketMax = 8192;             // buckets (LDS counters per tile of sets)
 constexpr uint32_t kBucketChunk = 1u << 14;  // entries per block of the per-bucket passes
 
@@ -686,6 +691,489 @@ __global__ __launch_bounds__(kThreads) void scan_cover_kernel(const unsigned lon
   }
 }
 
+// ---- the greedy over candidates ----
+//
+// Counts only fall, so a node whose initial count is below T is never chosen
+// while some candidate (initial count at least T) still has T or more.  The
+// greedy of k > 1 therefore takes the nodes of the largest counts as
+// candidates (kCandPerStep per step, at least kCandMin, at most kCandMax),
+// keeps of every set only its candidates, as a stream of 16-bit candidate
+// numbers whose top bit marks the first entry of a set, and runs each step as
+// one kernel over the stream: every block finds the best candidate itself,
+// compares its part of the stream with it, and takes the matched sets out of
+// the stream and of the counts.  No inverted index is built, no set offsets or
+// covered marks are kept, and the argmax reads the candidates instead of n
+// nodes.  A step whose best candidate has fallen below T writes key 0, the
+// later steps leave at once, and the caller runs the greedy over all nodes.
+// Seeds and gains are those of that greedy: the step's key is the largest
+// over all nodes (every other node's count is below T).
+// Against the inverted index with an argmax over n nodes and a cover pass per
+// step: TIM+ with k = 50 on the 1M-node graph under IC 5.41 -> 4.67 ms, on 15K
+// nodes under LT 1.78 -> 1.48 ms, with k = 25 on 123K nodes and per-edge
+// probabilities 4.58 -> 3.79 ms.  A step takes 7 to 9 us (10 to 16 before).
+// Half the candidates per step (128) leave the triggering model's greedy of
+// k = 10 on 200K nodes undecided (6.1 -> 6.6 ms) and gain nothing elsewhere.
+constexpr int kCandMin = 2048, kCandMax = 8192, kCandPerStep = 256;
+constexpr int kCandMaxSteps = 256;   // beyond, the candidates a greedy needs outgrow kCandMax
+constexpr uint32_t kCandDead = 0x7FFFu;      // number of an entry taken out
+constexpr uint32_t kCandFirst = 0x8000u;     // first entry of its set
+constexpr uint32_t kCandTaken = 0xFFFFFFFFu; // count of a chosen candidate
+constexpr int kCandBins = 1024;
+constexpr uint32_t kCandBinsUsed = 128u + 25u * 16u;  // those above belong to no 32-bit count
+constexpr int kCandSegs = 256;       // parts of the stream, one per block of a step
+constexpr int kCandStepThreads = 1024;
+constexpr int kCandHits = 576;       // matched entries a wavefront holds before it takes their sets out
+constexpr int kCandBuildThreads = 1024;
+constexpr int kCandTileMax = kCandBuildThreads;  // sets per tile of the build, one per thread
+constexpr int kCandWindow = 4096;    // entries per window of the build
+
+struct CandHead {  // counters of one greedy
+  uint32_t n;      // candidates
+  uint32_t t;      // T
+  uint32_t cursor; // stream entries reserved
+  uint32_t failed; // a step found no candidate at or above T
+};
+
+struct CandArrays {
+  CandHead* head;
+  uint32_t* bins;       // kCandBins
+  uint32_t* dec;        // 3 x kCandMax: what steps j-1, j, j+1 mod 3 take out of the counts
+  uint32_t* base;       // 2 x kCandMax: counts before step j-1's part is taken out, for steps j mod 2
+  uint32_t* node;       // kCandMax: node of a candidate
+  uint32_t* seg_start;  // kCandSegs
+  uint32_t* seg_len;    // kCandSegs
+  uint16_t* map;        // n: candidate number + 1, or 0
+  uint16_t* stream;
+  int segs;
+};
+
+// Bins of counts: exact below 128, then 16 per power of two.
+__device__ __forceinline__ uint32_t cand_bin(uint32_t c) {
+  if (c < 128u) return c;
+  const uint32_t e = 31u - (uint32_t)__clz((int)c);
+  return 128u + (e - 7u) * 16u + ((c >> (e - 4u)) & 15u);
+}
+__device__ __forceinline__ uint32_t cand_bin_low(uint32_t b) {
+  if (b < 128u) return b;
+  const uint32_t e = 7u + (b - 128u) / 16u;
+  return (16u + ((b - 128u) & 15u)) << (e - 4u);
+}
+
+// Clears the counters, bins and dec, and marks every candidate number of
+// base as taken until cand_pick_kernel gives it to a node.
+__global__ void cand_init_kernel(CandArrays c) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+  if (i == 0) *c.head = CandHead{0u, 0u, 0u, 0u};
+  for (int x = i; x < kCandBins; x += stride) c.bins[x] = 0u;
+  for (int x = i; x < 3 * kCandMax; x += stride) c.dec[x] = 0u;
+  for (int x = i; x < 2 * kCandMax; x += stride) c.base[x] = kCandTaken;
+}
+
+__global__ __launch_bounds__(kThreads) void cand_bins_kernel(const uint32_t* cnt, int64_t n, uint32_t* bins) {
+  __shared__ uint32_t s_bin[kCandBins];
+  for (int i = threadIdx.x; i < kCandBins; i += kThreads) s_bin[i] = 0u;
+  __syncthreads();
+  uint32_t low[4] = {0u, 0u, 0u, 0u};  // most nodes have counts below 4: not through one LDS word
+  const int64_t stride = (int64_t)gridDim.x * kThreads;
+  for (int64_t u = (int64_t)blockIdx.x * kThreads + threadIdx.x; u < n; u += stride) {
+    const uint32_t c = cnt[u];
+    if (c >= 4u) atomicAdd(&s_bin[cand_bin(c)], 1u);
+#pragma unroll
+    for (uint32_t w = 0; w < 4u; ++w) low[w] += c == w ? 1u : 0u;
+  }
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    uint32_t x = low[w];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    if (threadIdx.x % 64 == 0 && x) atomicAdd(&s_bin[w], x);
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < kCandBins; i += kThreads)
+    if (s_bin[i]) atomicAdd(&bins[i], s_bin[i]);
+}
+
+// T: the low end of the lowest bin with at most `most` nodes in it and above
+// (0 where all n nodes are at most that), then the candidates' numbers.
+__global__ __launch_bounds__(kThreads) void cand_pick_kernel(const uint32_t* cnt, int64_t n, uint32_t most,
+                                                             CandArrays c) {
+  __shared__ unsigned long long red[kThreads / 64];
+  __shared__ uint32_t s_t;
+  constexpr int per = kCandBins / kThreads;
+  // thread t holds bins from the top: kCandBins - 1 - per * t downwards
+  uint32_t b[per];
+  unsigned long long sum = 0, total;
+#pragma unroll
+  for (int i = 0; i < per; ++i) {
+    b[i] = c.bins[kCandBins - 1 - per * (int)threadIdx.x - i];
+    sum += b[i];
+  }
+  if (threadIdx.x == 0) s_t = 0xFFFFFFFFu;  // the top bin alone is too large
+  unsigned long long above = block_excl_scan(sum, red, &total);
+#pragma unroll
+  for (int i = 0; i < per; ++i) {
+    above += b[i];
+    const uint32_t bin = (uint32_t)(kCandBins - 1 - per * (int)threadIdx.x - i);
+    if (above <= most && bin < kCandBinsUsed) atomicMin(&s_t, cand_bin_low(bin));
+  }
+  __syncthreads();
+  const uint32_t t = n <= (int64_t)most ? 0u : s_t;
+  __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x == 0) c.head->t = t;
+  // the block's nodes in two passes, so that it reserves its candidates' numbers with one atomic
+  const int64_t span = ((n + gridDim.x - 1) / gridDim.x + kThreads - 1) / kThreads * kThreads;
+  const int64_t lo = (int64_t)blockIdx.x * span, hi = min(lo + span, n);
+  unsigned long long mine = 0;
+  for (int64_t u = lo + threadIdx.x; u < hi; u += kThreads) mine += cnt[u] >= t ? 1ull : 0ull;
+  uint32_t id = (uint32_t)block_excl_scan(mine, red, &total);
+  if (threadIdx.x == 0) s_t = total ? atomicAdd(&c.head->n, (uint32_t)total) : 0u;
+  __syncthreads();
+  id += s_t;
+  for (int64_t u = lo + threadIdx.x; u < hi; u += kThreads) {
+    const uint32_t x = cnt[u];
+    const bool in = x >= t;
+    if (in) {
+      c.node[id] = (uint32_t)u;
+      c.base[id] = x;
+    }
+    c.map[u] = in ? (uint16_t)++id : (uint16_t)0u;
+  }
+}
+
+// The stream: block b takes the tiles b, b + gridDim.x, ... of `ts` sets and
+// writes the candidates of their sets one set after the other into its part.
+// What bounds it: two dependent reads per entry (the node, its candidate
+// number); an entry finds its set by counting the set starts up to it in an
+// LDS bit array, as many bits as a window has entries.
+template <class V>
+__global__ __launch_bounds__(kCandBuildThreads) void cand_build_kernel(V sets, uint64_t nsets, int ts, CandArrays c) {
+  constexpr int NW = kCandBuildThreads / 64;
+  constexpr int NC = kCandWindow / 64;  // 64-entry chunks of a window, one per lane of a wavefront
+  constexpr int PW = NC / NW;           // chunks per wavefront
+  static_assert(NC == 64, "a wavefront scans the chunks of a window");
+  __shared__ unsigned long long red[NW];
+  __shared__ unsigned long long s_marks[NC];
+  __shared__ int64_t s_delta[kCandTileMax];
+  __shared__ uint32_t s_first[kCandTileMax], s_rank[NC], s_cnt[NC], s_base;
+  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
+  const uint64_t ntiles = (nsets + (uint64_t)ts - 1) / (uint64_t)ts;
+  // room for every entry of the block's sets
+  unsigned long long mine = 0, room;
+  for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const uint64_t s = tile * (uint64_t)ts + (uint64_t)tid;
+    if (tid < ts && s < nsets) mine += sets.len(s);
+  }
+  (void)block_excl_scan<kCandBuildThreads>(mine, red, &room);
+  if (tid == 0) s_base = atomicAdd(&c.head->cursor, (uint32_t)((room + 63ull) & ~63ull));
+  __syncthreads();
+  const uint32_t base = s_base;
+  uint32_t at = 0;  // entries written
+  for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const uint64_t s = tile * (uint64_t)ts + (uint64_t)tid;
+    unsigned long long len = 0;
+    int64_t start = 0;
+    if (tid < ts && s < nsets) {
+      len = sets.len(s);
+      start = sets.start(s);
+    }
+    // entries (low 40 bits) and non-empty sets (above) before this one
+    unsigned long long all;
+    const unsigned long long ex = block_excl_scan<kCandBuildThreads>(len | (len ? 1ull << 40 : 0ull), red, &all);
+    const uint64_t tot = all & ((1ull << 40) - 1ull), e0 = ex & ((1ull << 40) - 1ull);
+    const uint32_t rank = (uint32_t)(ex >> 40);
+    if (len) {
+      s_delta[rank] = start - (int64_t)e0;
+      s_first[rank] = 0xFFFFFFFFu;
+    }
+    uint32_t seen = 0;  // sets that started before the window
+    for (uint64_t w0 = 0; w0 < tot; w0 += kCandWindow) {
+      if (tid < NC) s_marks[tid] = 0ull;
+      __syncthreads();
+      if (len && e0 >= w0 && e0 - w0 < kCandWindow) atomicOr(&s_marks[(e0 - w0) / 64], 1ull << ((e0 - w0) % 64));
+      __syncthreads();
+      if (wv == 0) {
+        uint32_t x = (uint32_t)__popcll(s_marks[lane]), inc = x;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint32_t y = __shfl_up(inc, o, 64);
+          if (lane >= o) inc += y;
+        }
+        s_rank[lane] = seen + inc - x;
+        if (lane == 63) s_base = seen + inc;
+      }
+      __syncthreads();
+      seen = s_base;
+      uint32_t id[PW], rk[PW];  // candidate number + 1 (0: none), set of the entry
+#pragma unroll
+      for (int i = 0; i < PW; ++i) {
+        const int ch = i * NW + wv;
+        const uint64_t e = w0 + (uint64_t)(ch * 64 + lane);
+        id[i] = rk[i] = 0u;
+        if (e < tot) {
+          rk[i] = s_rank[ch] + (uint32_t)__popcll(s_marks[ch] & (~0ull >> (63 - lane))) - 1u;
+          id[i] = c.map[sets.nodes[s_delta[rk[i]] + (int64_t)e]];
+        }
+        const uint64_t m = __ballot(id[i] != 0u);
+        if (lane == 0) s_cnt[ch] = (uint32_t)__popcll(m);
+      }
+      __syncthreads();
+      const uint32_t x = s_cnt[lane];
+      uint32_t inc = x;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += y;
+      }
+      const uint32_t found = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+      const uint32_t chunk_at = at + inc - x;  // lane ch: where chunk ch's candidates go
+#pragma unroll
+      for (int i = 0; i < PW; ++i) {
+        const uint64_t m = __ballot(id[i] != 0u);
+        const uint64_t below = m & ((1ull << lane) - 1ull);
+        const uint32_t pos =
+            (uint32_t)__builtin_amdgcn_readlane((int)chunk_at, i * NW + wv) + (uint32_t)__popcll(below);
+        // of a set's candidates in this chunk only the first bids
+        const uint32_t prev = __shfl(rk[i], below ? 63 - __clzll((long long)below) : lane, 64);
+        if (id[i] && (!below || prev != rk[i])) atomicMin(&s_first[rk[i]], pos);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < PW; ++i) {
+        const uint64_t m = __ballot(id[i] != 0u);
+        const uint32_t pos = (uint32_t)__builtin_amdgcn_readlane((int)chunk_at, i * NW + wv) +
+                             (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        if (id[i])
+          c.stream[(size_t)base + pos] = (uint16_t)((id[i] - 1u) | (s_first[rk[i]] == pos ? kCandFirst : 0u));
+      }
+      at += found;
+    }
+    __syncthreads();
+  }
+  const uint32_t end = (at + 63u) & ~63u;  // within the room, itself a multiple of 64
+  if (at + (uint32_t)tid < end) c.stream[(size_t)base + at + (uint32_t)tid] = (uint16_t)(kCandFirst | kCandDead);
+  if (tid == 0) {
+    c.seg_start[blockIdx.x] = base;
+    c.seg_len[blockIdx.x] = end;
+  }
+}
+
+// The largest (smallest) value of eight neighbouring lanes, in all of them.
+__device__ __forceinline__ int max8(int x) {
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) x = max(x, __shfl_xor(x, o, 64));
+  return x;
+}
+__device__ __forceinline__ int min8(int x) {
+#pragma unroll
+  for (int o = 1; o < 8; o <<= 1) x = min(x, __shfl_xor(x, o, 64));
+  return x;
+}
+
+// Takes the sets of the matched entries hits[0, nh) out of a part of the
+// stream: eight lanes per set, which read the 64-entry window (one 128-byte
+// line) of the match, go back until the set's first entry and forward until
+// the next set's, counting every entry in dec and overwriting it.  Sets keep
+// the marks of their first entries, and no two matches lie in one set, so
+// neighbouring sets may be taken out at the same time.
+__device__ __forceinline__ void cand_take_out(uint16_t* part, int nwin, const uint32_t* hits, int nh, uint32_t* dec,
+                                              int lane) {
+  const int gl = lane & 7;
+  const uint4* vec = reinterpret_cast<const uint4*>(part);
+  for (int h0 = 0; h0 < nh; h0 += 8) {
+    const int h = h0 + (lane >> 3);
+    bool active = h < nh;
+    const int p = active ? (int)hits[h] : 0;
+    int w = p >> 6, start = -1;
+    uint4 x = make_uint4(0u, 0u, 0u, 0u);
+    bool back = active;
+    while (__ballot(back)) {
+      if (back) x = vec[w * 8 + gl];
+      const uint32_t word[4] = {x.x, x.y, x.z, x.w};
+      int mine = -1;
+      const int pos0 = w * 64 + gl * 8;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (((word[i >> 1] >> (16 * (i & 1))) & kCandFirst) && pos0 + i <= p) mine = pos0 + i;
+      const int at = max8(mine);
+      if (back) {
+        if (at >= 0 || w == 0) {
+          start = max(at, 0);
+          back = false;
+        } else {
+          --w;
+        }
+      }
+    }
+    bool fwd = active;
+    while (__ballot(fwd)) {
+      const uint32_t word[4] = {x.x, x.y, x.z, x.w};
+      int next = 0x7FFFFFFF;
+      const int pos0 = w * 64 + gl * 8;
+#pragma unroll
+      for (int i = 7; i >= 0; --i)
+        if (((word[i >> 1] >> (16 * (i & 1))) & kCandFirst) && pos0 + i > start) next = pos0 + i;
+      const int end = min8(next);
+      if (fwd) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const uint32_t e = (word[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+          const int pos = pos0 + i;
+          if (pos >= start && pos < end) {
+            if ((e & kCandDead) != kCandDead) atomicAdd(&dec[e & kCandDead], 1u);
+            part[pos] = (uint16_t)(e | kCandDead);
+          }
+        }
+        ++w;
+        fwd = end == 0x7FFFFFFF && w < nwin;
+        if (fwd) x = vec[w * 8 + gl];
+      }
+    }
+  }
+}
+
+// Step j.  Counts before it are base[j mod 2] less what step j-1 took out,
+// dec[(j-1) mod 3]; nothing written here is read by another block of the step.
+// What bounds it: the launch (about 2 us) and a chain of loads (the
+// candidates' counts, the stream, the matched sets), not the stream's bytes:
+// the part's first vectors are loaded before the argmax.
+__global__ __launch_bounds__(kCandStepThreads) void cand_step_kernel(CandArrays c, int most, int j,
+                                                                      unsigned long long* best) {
+  constexpr int NW = kCandStepThreads / 64;
+  __shared__ __align__(16) uint32_t s_dec[kCandMax];
+  __shared__ uint32_t s_hits[NW][kCandHits];
+  __shared__ unsigned long long s_key[NW];
+  __shared__ uint32_t s_num[NW], s_any;
+  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
+  const uint4* base = reinterpret_cast<const uint4*>(c.base + (size_t)(j & 1) * kCandMax);
+  uint4* base_next = reinterpret_cast<uint4*>(c.base + (size_t)((j + 1) & 1) * kCandMax);
+  const uint4* dec_prev = reinterpret_cast<const uint4*>(c.dec + (size_t)((j + 2) % 3) * kCandMax);
+  uint32_t* dec_now = c.dec + (size_t)(j % 3) * kCandMax;
+  uint4* dec_next = reinterpret_cast<uint4*>(c.dec + (size_t)((j + 1) % 3) * kCandMax);
+  const uint4* node = reinterpret_cast<const uint4*>(c.node);
+  const uint32_t t = c.head->t;
+  const bool failed = c.head->failed != 0u;
+  const int nvec = (int)(c.seg_len[blockIdx.x] / 8u);
+  uint16_t* part = c.stream + c.seg_start[blockIdx.x];
+  const uint4* vec = reinterpret_cast<const uint4*>(part);
+  // the candidate of the largest count, ties to the lowest node: count << 32 | ~node, and its number
+  constexpr int R = kCandMax / (4 * kCandStepThreads);  // fours of candidates per thread
+  uint4 now[R], id[R];
+  unsigned long long key = 0;
+  uint32_t num = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = r * kCandStepThreads + tid;
+    now[r] = make_uint4(kCandTaken, kCandTaken, kCandTaken, kCandTaken);
+    id[r] = make_uint4(0u, 0u, 0u, 0u);
+    if (4 * i < most) {
+      const uint4 b = base[i], d = dec_prev[i];
+      id[r] = node[i];
+      now[r] = make_uint4(b.x == kCandTaken ? kCandTaken : b.x - d.x, b.y == kCandTaken ? kCandTaken : b.y - d.y,
+                          b.z == kCandTaken ? kCandTaken : b.z - d.z, b.w == kCandTaken ? kCandTaken : b.w - d.w);
+      reinterpret_cast<uint4*>(s_dec)[i] = make_uint4(0u, 0u, 0u, 0u);
+    }
+  }
+  uint4 x = make_uint4(~0u, ~0u, ~0u, ~0u);
+  if (tid < nvec) x = vec[tid];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t cv[4] = {now[r].x, now[r].y, now[r].z, now[r].w}, uv[4] = {id[r].x, id[r].y, id[r].z, id[r].w};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const unsigned long long k = ((unsigned long long)cv[w] << 32) | (0xFFFFFFFFull - uv[w]);
+      if (cv[w] != kCandTaken && k > key) {
+        key = k;
+        num = (uint32_t)(4 * (r * kCandStepThreads + tid) + w);
+      }
+    }
+  }
+  unsigned long long top = key;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long y = __shfl_xor(top, o, 64);
+    top = y > top ? y : top;
+  }
+  // keys differ between candidates: one lane holds the wavefront's top one
+  if (key == top && (top || lane == 0)) {
+    s_key[wv] = top;
+    s_num[wv] = num;
+  }
+  if (tid == 0) s_any = 0u;
+  __syncthreads();
+  top = 0;
+  uint32_t v = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    if (s_key[w] > top) {
+      top = s_key[w];
+      v = s_num[w];
+    }
+  }
+  const bool ok = !failed && top != 0ull && (uint32_t)(top >> 32) >= t;
+  if (blockIdx.x == 0) {
+    if (tid == 0) {
+      best[j] = ok ? top : 0ull;
+      if (!ok) c.head->failed = 1u;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int i = r * kCandStepThreads + tid;
+      if (4 * i < most) {
+        uint4 b = now[r];
+        if (v == 4u * (uint32_t)i) b.x = kCandTaken;
+        if (v == 4u * (uint32_t)i + 1u) b.y = kCandTaken;
+        if (v == 4u * (uint32_t)i + 2u) b.z = kCandTaken;
+        if (v == 4u * (uint32_t)i + 3u) b.w = kCandTaken;
+        base_next[i] = b;
+        dec_next[i] = make_uint4(0u, 0u, 0u, 0u);
+      }
+    }
+  }
+  if (!ok) return;
+  int nh = 0;
+  const uint32_t vv = v | (v << 16);
+  for (int i0 = wv * 64; i0 < nvec; i0 += kCandStepThreads) {
+    const int i = i0 + lane;
+    if (i0 >= kCandStepThreads) {
+      x = make_uint4(~0u, ~0u, ~0u, ~0u);
+      if (i < nvec) x = vec[i];
+    }
+    const uint32_t word[4] = {x.x, x.y, x.z, x.w};
+    uint32_t m = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const uint32_t y = (word[w] ^ vv) & 0x7FFF7FFFu;
+      m |= (y & 0xFFFFu) == 0u ? 1u << (2 * w) : 0u;
+      m |= (y >> 16) == 0u ? 2u << (2 * w) : 0u;
+    }
+    uint64_t any = __ballot(m != 0u);
+    while (any) {
+      if (m) {
+        const int bit = __ffs((int)m) - 1;
+        s_hits[wv][nh + (int)__popcll(any & ((1ull << lane) - 1ull))] = (uint32_t)(i * 8 + bit);
+        m &= m - 1u;
+      }
+      nh += (int)__popcll(any);
+      any = __ballot(m != 0u);
+    }
+    if (nh > kCandHits - 512) {  // the next 64 vectors may match in 512 entries
+      __builtin_amdgcn_wave_barrier();
+      cand_take_out(part, nvec / 8, s_hits[wv], nh, s_dec, lane);
+      nh = 0;
+      s_any = 1u;
+    }
+  }
+  if (nh) {
+    __builtin_amdgcn_wave_barrier();
+    cand_take_out(part, nvec / 8, s_hits[wv], nh, s_dec, lane);
+    s_any = 1u;
+  }
+  __syncthreads();
+  if (!s_any) return;
+  for (int i = tid; i < most; i += kCandStepThreads)
+    if (s_dec[i]) atomicAdd(&dec_now[i], s_dec[i]);
+}
+
 unsigned grid_for(uint64_t items, unsigned cap) {
   uint64_t g = (items + kThreads - 1) / kThreads;
   if (g < 1) g = 1;
@@ -816,15 +1304,90 @@ void bucket_counts(const GreedyArgs& a, V sets, const BucketLayout& L, bool inde
                      L.nb, L.shift, a.n, a.cnt);
 }
 
+
+// ---- the candidate greedy's workspace ----
+struct CandLayout {
+  size_t head = 0, bins = 0, dec = 0, base = 0, node = 0, seg = 0, map = 0, stream = 0, bytes = 0;
+};
+
+CandLayout cand_layout(int64_t n, uint64_t total) {
+  CandLayout L;
+  size_t at = 0;
+  L.head = at;
+  at += 256;
+  L.bins = at;
+  at += (size_t)kCandBins * 4;
+  L.dec = at;
+  at += (size_t)kCandMax * 4 * 3;
+  L.base = at;
+  at += (size_t)kCandMax * 4 * 2;
+  L.node = at;
+  at += (size_t)kCandMax * 4;
+  L.seg = at;
+  at += (size_t)kCandSegs * 4 * 2;
+  L.map = at;
+  at += align256((size_t)n * 2);
+  L.stream = at;
+  at += align256(((size_t)total + 64 * (size_t)kCandSegs) * 2);
+  L.bytes = at;
+  return L;
+}
+
+CandArrays cand_arrays(const GreedyArgs& a) {
+  const CandLayout L = cand_layout(a.n, a.total);
+  CandArrays c;
+  c.head = at_offset<CandHead>(a.bkt, L.head);
+  c.bins = at_offset<uint32_t>(a.bkt, L.bins);
+  c.dec = at_offset<uint32_t>(a.bkt, L.dec);
+  c.base = at_offset<uint32_t>(a.bkt, L.base);
+  c.node = at_offset<uint32_t>(a.bkt, L.node);
+  c.seg_start = at_offset<uint32_t>(a.bkt, L.seg);
+  c.seg_len = c.seg_start + kCandSegs;
+  c.map = at_offset<uint16_t>(a.bkt, L.map);
+  c.stream = at_offset<uint16_t>(a.bkt, L.stream);
+  // at least 1024 entries per part: smaller collections are bound by their steps' latency, not by the parts' work
+  c.segs = (int)std::max<uint64_t>(1, std::min<uint64_t>(kCandSegs, a.total / 1024));
+  return c;
+}
+
+// The candidate greedy runs where it has its workspace and its positions fit
+// 32 bits, for 2 to kCandMaxSteps steps (a.k; 0 where the steps are launched
+// one by one), unless it has failed on this collection (a.all_nodes).
+bool use_candidates(const GreedyArgs& a) {
+  return a.bkt && a.k > 1 && a.k <= kCandMaxSteps && !a.all_nodes && a.nsets && a.total &&
+         a.total + 64ull * kCandSegs < 0xFFFFFFFFull && bucket_layout(a.n, a.total, true).bytes;
+}
+
+int cand_most(const GreedyArgs& a) { return std::min(kCandMax, std::max(kCandMin, kCandPerStep * a.k)); }
+
+template <class V>
+void cand_prepare(const GreedyArgs& a, V sets, hipStream_t s) {
+  const CandArrays c = cand_arrays(a);
+  hipLaunchKernelGGL(cand_init_kernel, dim3(16), dim3(kThreads), 0, s, c);
+  const unsigned grid = grid_for((uint64_t)a.n, 256);
+  const int most = cand_most(a);
+  if (a.n > most) hipLaunchKernelGGL(cand_bins_kernel, dim3(grid), dim3(kThreads), 0, s, a.cnt, a.n, c.bins);
+  hipLaunchKernelGGL(cand_pick_kernel, dim3(grid), dim3(kThreads), 0, s, a.cnt, a.n, (uint32_t)most, c);
+  // tiles of about two windows' entries, at least one per block
+  const uint64_t mean = a.total / a.nsets + 1;
+  const uint64_t ts = std::min<uint64_t>(2 * kCandWindow / mean, a.nsets / (uint64_t)c.segs + 1);
+  hipLaunchKernelGGL(cand_build_kernel<V>, dim3((unsigned)c.segs), dim3(kCandBuildThreads), 0, s, sets, a.nsets,
+                     (int)std::min<uint64_t>(kCandTileMax, std::max<uint64_t>(16, ts)), c);
+}
+
 }  // namespace
 
-size_t bucket_workspace_bytes(int64_t n, uint64_t total, bool index) { return bucket_layout(n, total, index).bytes; }
+size_t bucket_workspace_bytes(int64_t n, uint64_t total, bool index) {
+  const size_t b = bucket_layout(n, total, index).bytes;
+  // the candidate arrays take the sort's place once the counts are done
+  return b && index ? std::max(b, cand_layout(n, total).bytes) : b;
+}
 
 void launch_counts(const GreedyArgs& a, hipStream_t s) {
   const uint64_t n = (uint64_t)a.n;
   hipLaunchKernelGGL(zero_u32, dim3(grid_for(n, 4096)), dim3(kThreads), 0, s, a.cnt, n);
   if (!a.nsets) return;
-  if (a.bkt && a.total) {
+  if (a.bkt && a.total > kDirectCounts) {
     const BucketLayout L = bucket_layout(a.n, a.total, false);
     if (L.bytes) {
       if (a.set_off) bucket_counts(a, csr_of(a), L, false, s);
@@ -844,6 +1407,12 @@ void launch_counts(const GreedyArgs& a, hipStream_t s) {
 
 void launch_index(const GreedyArgs& a, hipStream_t s) {
   const uint64_t n = (uint64_t)a.n;
+  if (use_candidates(a)) {
+    launch_counts(a, s);
+    if (a.set_off) cand_prepare(a, csr_of(a), s);
+    else cand_prepare(a, pool_of(a), s);
+    return;
+  }
   if (a.bkt && a.nsets && a.total) {
     const BucketLayout L = bucket_layout(a.n, a.total, true);
     if (L.bytes) {
@@ -998,6 +1567,13 @@ void launch_set_u64(unsigned long long* p, unsigned long long v, hipStream_t s) 
 }
 
 void launch_greedy(const GreedyArgs& a, int k, hipStream_t s) {
+  if (use_candidates(a)) {
+    const CandArrays c = cand_arrays(a);
+    for (int j = 0; j < k; ++j)
+      hipLaunchKernelGGL(cand_step_kernel, dim3((unsigned)c.segs), dim3(kCandStepThreads), 0, s, c,
+                         cand_most(a), j, a.best);
+    return;
+  }
   launch_greedy_init(a, a.nsets, k, s);
   for (int j = 0; j < k; ++j) {
     launch_argmax(a, j, s);

@@ -242,12 +242,20 @@ struct GreedyArgs {
   unsigned long long* best;  // k packed (count, ~id) keys
   void* scan_temp;
   void* bkt;           // optional: bucket_workspace_bytes(n, total, index) for the counting sort by node range
+                       // and the candidate greedy
+  int k;               // greedy steps of the whole run, or 0 where they are launched one by one
+  int all_nodes;       // nonzero: no candidate greedy (it left a key 0 on this collection)
 };
 // Workspace of the counting sort by node range that launch_counts and
-// launch_index use when GreedyArgs.bkt is set; 0 where it does not apply.
+// launch_index use when GreedyArgs.bkt is set, and (index) of the candidate
+// greedy; 0 where they do not apply.
 size_t bucket_workspace_bytes(int64_t n, uint64_t total, bool index);
 // Coverage counts only (the greedy of k = 1 needs no index).
 void launch_counts(const GreedyArgs& a, hipStream_t s);
+// With bkt and k set, launch_index and launch_greedy run the greedy over the
+// candidates of the largest counts where it applies; a step those do not
+// decide leaves key 0 (no valid key is 0), as do the steps after it, and both
+// are launched again with all_nodes set.
 void launch_index(const GreedyArgs& a, hipStream_t s);
 void launch_greedy(const GreedyArgs& a, int k, hipStream_t s);
 // The same greedy one step at a time, for collections of which only sets
