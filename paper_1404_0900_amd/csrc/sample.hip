@@ -60,9 +60,12 @@ __device__ __forceinline__ void wave_sync() {
 // device-atomic results that lane 0 fetched for the whole wavefront.  Through
 // __shfl the compiler keeps them, and what is derived from them, in vector
 // registers.
+// (The builtin returns a signed int: each half goes through uint32_t, or a low
+// word of 2^31 or more would fill the high word with ones.)
 __device__ __forceinline__ unsigned long long lane0_u64(unsigned long long x) {
-  return ((unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(x >> 32)) << 32) |
-         (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)x);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+  return ((unsigned long long)hi << 32) | (unsigned long long)lo;
 }
 
 // x from the lane O below in the same 16-lane DPP row (0 where that leaves the row).
