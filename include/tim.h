@@ -183,8 +183,9 @@ tim_status tim_set_resident_limit(tim_ctx *ctx, uint64_t max_sets);
 /* What tim_autotune measured and chose. */
 typedef struct {
   int32_t seg_lanes;   /* lanes per IC set in the first sampler tier: 4, 8, 16, 32 or 64 (with it come
-                          the sizes a set may reach before a later tier takes it: a 64/128/128/256/512-
-                          node queue and 256/512/512/1024/2048 four-edge groups) */
+                          the sizes a set may reach before a later tier takes it: a 64/160/128/256/512-
+                          node queue and 256/4096/512/1024/2048 four-edge groups; 8 is the shape that deals
+                          the groups of sixteen sets over a wavefront) */
   uint32_t slice_cap;  /* largest node-pool slice a wavefront reserves when storing sets */
   double ms_width[5];  /* IC: one width-mode launch of `sets` sets with 4, 8, 16, 32, 64 lanes (0 for LT) */
   double ms_emit[4];   /* one stored-set launch with slice caps 512, 1024, 2048, 4096 */
@@ -226,8 +227,8 @@ typedef struct {
   tim_kernel_profile sampler[2][3]; /* [model][0: widths, 1: stored sets, 2: coverage] */
   uint64_t index_calls;             /* inverted-index builds + greedy runs */
   double index_ms, greedy_ms;
-  tim_kernel_profile ic_wide[3];    /* IC launches of fewer than 262144 sets (widths, coverage), which run
-                                       the 64-lane first tier; sampler[0][] holds the others */
+  tim_kernel_profile ic_wide[3];    /* IC launches of few sets (fewer than n / 20 and 262144), which run the
+                                       64-lane first tier; sampler[0][] holds the others */
   tim_kernel_profile grouped[2];    /* [model] multi-job launches that run several early KptEstimation rounds
                                        at once, one job per round; sets counts every set they sampled,
                                        those of rounds past the stopping one included */

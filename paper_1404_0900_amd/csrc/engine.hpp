@@ -110,7 +110,8 @@ struct SampleArgs {
 // ---- sample.hip ----
 void launch_clear_counters(unsigned long long* ctr, hipStream_t s);
 // Lanes per set of the IC tier-0 kernel: 4, 8, 16, 32 or 64 (environment
-// variable TIM_IC_SEG_LANES, read when a context is created; default 8).
+// variable TIM_IC_SEG_LANES, read when a context is created; default 8, the
+// shape that deals the groups of sixteen sets over a wavefront).
 int ic_seg_lanes();
 int ic_blocks_per_cu(int mode, bool wc, int seg_lanes);
 int ic_tier1_blocks_per_cu(int mode, bool wc);
@@ -131,7 +132,7 @@ void launch_sample(int model, int mode, const SampleArgs& a, int seg_lanes, int 
 
 // Sampling jobs of several queries in one launch (device array of njobs
 // SampleArgs, 1 <= njobs <= 64, one mode and model; all jobs point at the
-// same last-tier slots).  Tier 0 of IC uses 8 lanes per set.
+// same last-tier slots).  Tier 0 of IC uses the default shape.
 struct JobTable {
   const SampleArgs* jobs;
   int njobs;

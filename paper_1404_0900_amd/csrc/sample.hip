@@ -1,21 +1,19 @@
 // RR-set samplers for gfx950 (Definitions 1-2; Section 3.1; Section 4.2).
 //
-// IC (reverse BFS over in-edges), tier 0: a wavefront is split into segments
-// of S lanes and every segment builds its own RR set, so one wavefront keeps
-// 64/S sets in flight and their memory latencies overlap.  A set's nodes live
-// in an LDS queue (which is also its output list); visited nodes are found
-// through an LDS membership signature (segments of up to 8 lanes) or an LDS
-// open-addressing hash (wider ones).  Each iteration of the loop, every segment either
-// loads its next batch of up to S queued nodes (two CSR offsets per lane, a
-// segmented prefix sum of their 4-edge groups) or processes S groups of the
-// current batch: a lane loads 4 consecutive sources with one 16-byte load,
-// draws one Philox block for the group and decides the 4 edges with its 4
-// words; live edges into unvisited nodes are appended to the queue.  Sets
-// that outgrow the segment's LDS structures are deferred: a set is a pure
-// function of its keys, so restarting it in another tier gives the same set.
-// Tier 1 is the same kernel with one set per wavefront and 8x the LDS
-// capacity; the last tier is a 512-thread block per set with visited stamps
-// and a queue of n entries in device memory.
+// IC (reverse BFS over in-edges).  In every tier a lane loads 4 consecutive
+// sources of an in-list with one 16-byte load, draws one Philox block for that
+// 4-edge group and decides the 4 edges with its 4 words; live edges into
+// unvisited nodes are appended to the set's queue, which is also its output
+// list.  The default first tier (ic_pool_run) keeps sixteen sets per wavefront
+// and deals their groups over all 64 lanes.  The others (ic_seg_run) split a
+// wavefront into segments of S lanes that build a set each: every segment loads
+// its next batch of up to S queued nodes (a segmented prefix sum of their
+// groups), then processes S groups at a time; visited nodes are found through an
+// LDS membership signature (S = 4) or an LDS open-addressing hash.  Sets that
+// outgrow a tier's LDS structures are deferred: a set is a pure function of its
+// keys, so restarting it in another tier gives the same set.  Tier 1 is the
+// one-set-per-wavefront segment kernel; the last tier is a 512-thread block per
+// set with visited stamps and a queue of n entries in device memory.
 //
 // General triggering (Section 4.2): one set per wavefront over an LDS queue
 // and hash; larger sets go to a block per set with device-memory stamps.
@@ -823,16 +821,418 @@ __device__ __forceinline__ void ic_seg_run(const SampleArgs& a, const TierIO& io
 }
 
 // Single launches only (launch_ic): their tiers 0 and 1 take sets from kCtrParts cursors.
-// The modes that store no nodes ask for 7 wavefronts per SIMD: the 8-lane shape then fits
-// 71 VGPRs without spilling and its width launches run about 3% faster.  The storing mode
-// needs 80 and stays at 6 (held to 72 it spills).  Shapes with larger queues are held to 5
-// or 6 by their LDS and ignore the request.
 template <int MODE, bool WC, int S, int Q, int HLOG, int GMAX, int R>
-__global__ __launch_bounds__(kSegThreads) __attribute__((amdgpu_waves_per_eu(MODE == kModeEmit ? 1 : 7, 8)))
-void ic_seg_kernel(SampleArgs a, TierIO io) {
+__global__ __launch_bounds__(kSegThreads) void ic_seg_kernel(SampleArgs a, TierIO io) {
   __shared__ BlockAcc blk;
   block_acc_init(blk);
   ic_seg_run<MODE, WC, S, Q, HLOG, GMAX, R, true>(a, io, true, &blk);
+}
+
+// ------------------------------------------------------------------------
+// IC, tier 0 for launches that fill the chip: a wavefront keeps 64 / kPoolLanes
+// sets in flight and deals the 4-edge groups of all of them over its 64 lanes.
+// Fetching: the kPoolLanes lanes of a set take its next queued nodes, and the
+// nodes' groups are lined up behind those still waiting, one descriptor per
+// node in an LDS ring and a mark in an LDS bit ring where its groups start.
+// Deciding: 64 groups at a time, a lane finding its node by counting the marks
+// up to it; fewer than 64 wait for the next fetch while any others were decided.
+// A node of kPoolWide groups or more is decided by the whole wavefront at once,
+// beside the ring, so that a hub's in-list costs no more per group than others.
+// A set's nodes (its queue and what is stored) lie in LDS blocks of kPoolBlock:
+// the first is the set's own, the others come from a few the wavefront's sets
+// share, since few sets in flight are large; a set that finds none, or outgrows
+// kPoolQ nodes or kPoolGroups groups, is deferred.
+//
+// What bounds it: VALU issue (2.8 instructions per examined edge in width mode
+// on the 1M-node graph, 75% of the issue slots), then the chain of an iteration
+// (queue, offsets, sources, signature).  Eight lanes per set with the groups of a
+// set dealt over its own lanes, the shape before this one, took 4.6 instructions
+// per edge: a lane had a group in 28 of 64.  LDS decides how many wavefronts hide
+// the chain, hence the shared blocks: queues of 128 nodes per set leave 3
+// wavefronts per SIMD and 96 nodes (with half the signature) 4, where a TIM+ run
+// with k = 1 on the 1M-node graph took 33.2 and 30.9 ms; with blocks 5 wavefronts
+// fit, and it takes 27.2 ms (33.7 with eight lanes per set).  Half the signature
+// or 24 shared blocks: 29.2 and 29.6 against 28.7 ms; thresholds of the weighted
+// cascade from an LDS table instead of a 64-bit product per edge: 28.3 against
+// 27.2 ms.
+// ------------------------------------------------------------------------
+constexpr int kPoolLanes = 4;
+constexpr int kPoolBlock = 32;
+constexpr int kPoolShared = 16;                    // blocks the wavefront's sets share (at most 32)
+constexpr int kPoolQ = 5 * kPoolBlock;             // largest set: its own block and four more
+constexpr int kPoolSigLog = 5;                     // signature words per set: 2^5 (1024 bits)
+constexpr uint32_t kPoolGroups = 4096;
+constexpr uint32_t kPoolWide = 32;                 // (16: 28.5 against 27.2 ms)
+constexpr int kPoolRing = 128;  // descriptors: 64 waiting at most (one per waiting group, one cut by the line), 64 fetched
+constexpr int kPoolMarks = 32;  // 64-bit words: 63 groups waiting and 64 nodes of 31
+// Complete sets are finished, stored and replaced kPoolFinish at a time: the
+// k = 1 run above takes 28.0 ms one at a time, 27.5 with 3, 27.2 with 4.
+constexpr int kPoolFinish = 4;
+constexpr uint32_t kPoolOver = 1u << 20;           // added to the length of a set that found no block
+static_assert(63 + 64 * (kPoolWide - 1) <= 64 * kPoolMarks, "the bit ring holds what can wait");
+
+template <int MODE, bool WC, bool SPLIT>
+__device__ __forceinline__ void ic_pool_run(const SampleArgs& a, const TierIO& io, BlockAcc* blk) {
+  constexpr int SL = kPoolLanes, NS = kWave / SL, NW = kSegThreads / kWave, Q = kPoolQ, B = kPoolBlock;
+  constexpr int SIGW = 1 << kPoolSigLog;
+  static_assert(SL == 4 && NS == 16 && Q == 5 * B, "a set's lanes free its four shared blocks, descriptors hold 4-bit sets");
+  __shared__ int32_t s_node[NW][(NS + kPoolShared) * B];
+  __shared__ __align__(16) uint32_t s_sig[NW * NS][SIGW];
+  // a node's first edge; its first group's number (11 bits, mod 2048), in-degree (7 bits: under kPoolWide groups)
+  // and set (4 bits)
+  __shared__ uint2 s_ring[NW][kPoolRing];
+  __shared__ unsigned long long s_marks[NW][kPoolMarks];
+  __shared__ uint32_t s_tail[NW * NS];  // nodes of the set; beyond Q once it has outgrown the tier
+  __shared__ uint32_t s_tab[NW * NS];   // its shared blocks, 8 bits each
+  __shared__ uint32_t s_rel[NW * NS];   // its relative id
+  __shared__ uint32_t s_hit[MODE == kModeCover ? NW * NS : 1];
+  __shared__ uint4 s_fin[MODE == kModeEmit ? NW : 1][NS];  // sets to be copied: row and length, blocks, place in the pool
+  const int lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
+  const int sl = lane % SL, sw = lane / SL, leader = sw * SL, seg = wv * NS + sw;
+  const bool is_leader = sl == 0;
+  const uint64_t below_leader = leader ? (~0ull >> (64 - leader)) : 0ull;
+  const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
+  int32_t* nodes = s_node[wv];
+  const GraphView g = a.g;
+  const Key key = make_key(a.seed);
+  const unsigned long long total = a.count;
+  const uint32_t first_lo = (uint32_t)a.first, first_hi = (uint32_t)(a.first >> 32);
+  if (lane < kPoolMarks) s_marks[wv][lane] = 0ull;
+  Acc acc;
+  Reservoir res;
+  res.chunk = chunk_for(total, NW, NS);
+  if (SPLIT) res.part = (int)(blockIdx.x % (unsigned)kCtrParts);  // blocks take turns over the XCDs
+  RootBuffer rb;
+  unsigned long long pool_next = 0, pool_end = 0;  // wavefront's slice of the node pool
+  uint32_t prod = 0, cons = 0;    // groups lined up and decided (cons a multiple of 64)
+  uint32_t nprod = 0, nseen = 0;  // descriptors written, and those whose groups start before cons
+  uint32_t free_blocks = (uint32_t)((1ull << kPoolShared) - 1ull);
+
+  // set state (the same in every lane of a set)
+  bool has = false, exhausted = false;
+  uint32_t rel = 0, last_end = 0, gsum = 0;  // last_end: number of the group after its last one lined up
+  uint32_t tab = 0, nblk = 0;                // its shared blocks
+  int head = 0;
+  uint32_t wlane = 0;  // this lane's part of the width
+
+  // where node p of a set lies, given its row in the wavefront and its shared blocks
+  auto place = [&](int row, uint32_t blocks, uint32_t p) -> uint32_t {
+    const uint32_t b = p / B;
+    const uint32_t id = b ? (uint32_t)NS + ((blocks >> (8u * (b - 1u))) & 255u) : (uint32_t)row;
+    return id * B + p % B;
+  };
+
+  for (;;) {
+    // ---- A: complete sets are finished (or deferred) once none of their
+    // groups waits, kPoolFinish of them at a time while others have work left
+    const uint32_t now = has ? s_tail[seg] : 0u;
+    const bool over = now > (uint32_t)Q || gsum > kPoolGroups;
+    const bool hit = MODE == kModeCover && has && s_hit[seg] != 0u;
+    const bool complete = has && (int)(last_end - cons) <= 0 && (over || hit || head >= (int)now);
+    const uint64_t busy = __ballot(has && !complete);
+    if (busy == 0ull || __popcll(__ballot(complete)) >= SL * kPoolFinish) {
+      bool fin = false, defer_now = false;
+      uint32_t fin_len = 0, fin_width = 0;
+      if (complete) {
+        fin_width = seg_sum_u32<SL>(wlane);
+        has = false;
+        if (over) {
+          defer_now = true;
+        } else {
+          fin = true;
+          fin_len = now;
+          if (is_leader && MODE != kModeEmit) {
+            if (MODE == kModeWidth) {
+              a.wbuf[rel] = fin_width;
+              if (a.sizes) a.sizes[rel] = fin_len;
+            }
+            acc.width += fin_width;
+            acc.nodes += fin_len;
+            if (hit) acc.covered += 1;
+          }
+        }
+      }
+      const bool done = fin || defer_now;
+      {
+        const bool dl = defer_now && is_leader;
+        const uint64_t dm = __ballot(dl);
+        if (dm) {
+          unsigned long long base = 0;
+          if (lane == 0) base = atomicAdd(&a.ctr[io.out_len_ctr], (unsigned long long)__popcll(dm));
+          base = lane0_u64(base);
+          if (dl) {
+            const unsigned long long pos = base + (unsigned long long)__popcll(dm & below);
+            if (pos < a.count) io.out_list[pos] = rel;
+          }
+        }
+      }
+      if (MODE == kModeEmit) {  // stored sets: one reservation in the wavefront's pool slice per iteration
+        const uint32_t mine = (fin && is_leader) ? fin_len : 0u;
+        const uint64_t fm = __ballot(mine != 0u);
+        if (fm) {
+          const uint32_t winc = seg_incl_scan<kWave>(mine, lane);
+          const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)winc, kWave - 1);
+          const unsigned long long my_base =
+              pool_place(a, (unsigned long long)a.pool_chunk, mine, winc, tot, pool_next, pool_end, lane);
+          if (fin && is_leader) {
+            const bool fits = my_base + fin_len <= a.pool_cap;
+            s_fin[wv][__popcll(fm & below)] =
+                make_uint4((uint32_t)sw | ((fits ? fin_len : 0u) << 8), tab, (uint32_t)my_base, (uint32_t)(my_base >> 32));
+            a.set_start[rel] = a.pool_base + my_base;
+            a.set_len[rel] = fin_len;
+            if (a.widths) a.widths[rel] = fin_width;
+            if (a.wbuf) a.wbuf[rel] = fin_width;
+            acc.width += fin_width;
+            acc.nodes += fin_len;
+          }
+          wave_sync();
+          // sixteen lanes copy a set: most have at most as many nodes
+          for (int r = lane / 16; r < __popcll(fm); r += kWave / 16) {
+            const uint4 f = s_fin[wv][r];
+            int32_t* to = a.pool + (((unsigned long long)f.w << 32) | f.z);
+            for (uint32_t i = lane % 16; i < (f.x >> 8); i += 16) to[i] = nodes[place((int)(f.x & 255u), f.y, i)];
+          }
+        }
+      }
+      if (__ballot(done && nblk != 0u)) {  // their shared blocks are free again: lane sl of a set holds the sl-th
+        uint32_t bits = done && (uint32_t)sl < nblk ? 1u << ((tab >> (8 * sl)) & 31u) : 0u;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) bits |= __shfl_xor(bits, o);
+        free_blocks |= (uint32_t)__builtin_amdgcn_readfirstlane((int)bits);
+        if (done) nblk = 0u;
+      }
+      wave_sync();
+
+      // ---- B: idle sets' lanes take their next set
+      {
+        int32_t root = 0;
+        unsigned long long item = 0;
+        const bool want = !has && !exhausted;
+        if (take_set<SPLIT>(a, io, total, res, rb, want, is_leader, below_leader, lane, exhausted, item, root)) {
+          rel = (uint32_t)item;
+          const uint32_t hr = sig_hash(root), wd = hr >> (32 - kPoolSigLog), bt = 1u << ((hr >> (27 - kPoolSigLog)) & 31u);
+          uint4* s4 = reinterpret_cast<uint4*>(s_sig[seg]);
+          for (int i = sl; i < SIGW / 4; i += SL) {
+            const uint32_t w0 = 4u * (uint32_t)i;
+            s4[i] = make_uint4(wd == w0 ? bt : 0u, wd == w0 + 1u ? bt : 0u, wd == w0 + 2u ? bt : 0u,
+                               wd == w0 + 3u ? bt : 0u);
+          }
+          if (is_leader) {
+            nodes[sw * B] = root;
+            s_tail[seg] = 1u;
+            s_rel[seg] = rel;
+            if (MODE == kModeCover) s_hit[seg] = in_seed(a.seed_bits, root) ? 1u : 0u;
+          }
+          has = true;
+          head = 0;
+          last_end = cons;
+          gsum = 0;
+          wlane = 0;
+        }
+      }
+      if (__ballot(has) == 0) break;
+    }
+    wave_sync();
+
+    // ---- C: sets with queued nodes line up the groups of their next ones
+    uint32_t ea = 0, d = 0, ng = 0, x = 0;
+    bool wide = false;
+    if (has) {
+      const uint32_t tail = s_tail[seg];
+      const bool hit = MODE == kModeCover && s_hit[seg] != 0u;
+      if (tail <= (uint32_t)Q && gsum <= kPoolGroups && !hit) {
+        const int nb = min((int)tail - head, SL);
+        if (sl < nb) {
+          const int32_t v = nodes[place(sw, tab, (uint32_t)(head + sl))];
+          ea = g.off32[v];  // with off32[v + 1]: one 8-byte load
+          const uint32_t eb = g.off32[v + 1];
+          d = eb - ea;
+          ng = d ? ((eb - 1u) >> 2) - (ea >> 2) + 1u : 0u;
+        }
+        wlane += d;
+        head += nb;
+        gsum += seg_sum_u32<SL>(ng);
+        if (gsum <= kPoolGroups) {
+          wide = ng >= kPoolWide;
+          x = wide ? 0u : ng;
+        }
+      }
+    }
+    const uint32_t incl = seg_incl_scan<kWave>(x, lane);
+    const uint64_t xm = __ballot(x != 0u);
+    if (x) {
+      const uint32_t start = prod + incl - x;
+      const uint32_t rank = nprod + (uint32_t)__popcll(xm & below);
+      s_ring[wv][rank % kPoolRing] = make_uint2(ea, (start % 2048u) | (d << 11) | ((uint32_t)sw << 18));
+      atomicOr(&s_marks[wv][(start / 64u) % kPoolMarks], 1ull << (start % 64u));
+    }
+    {
+      const uint32_t seg_end = __shfl(incl, leader + SL - 1);
+      if (seg_bits<SL>(xm, sw) != 0ull) last_end = prod + seg_end;
+    }
+    prod += (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+    nprod += (uint32_t)__popcll(xm);
+    wave_sync();
+
+    // ---- D: wide nodes first, then the line in steps of 64 groups
+    uint64_t wm = __ballot(wide);
+    uint32_t wg = 0;  // groups of the wide node decided
+    bool worked = false;
+    for (;;) {
+      uint32_t oa, od, grp;  // the node's first edge and in-degree, this lane's group
+      int orow;              // the set's row in the wavefront
+      bool on;
+      if (wm) {
+        const int src = __ffsll((unsigned long long)wm) - 1;
+        oa = (uint32_t)__builtin_amdgcn_readlane((int)ea, src);
+        od = (uint32_t)__builtin_amdgcn_readlane((int)d, src);
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)ng, src);
+        on = wg + (uint32_t)lane < n;
+        grp = (oa >> 2) + wg + (uint32_t)lane;
+        orow = src / SL;
+        wg += kWave;
+        if (wg >= n) {
+          wm &= wm - 1ull;
+          wg = 0;
+        }
+      } else {
+        const uint32_t avail = prod - cons;
+        if (avail == 0u || (avail < (uint32_t)kWave && worked)) break;
+        const uint32_t word = (cons / 64u) % kPoolMarks;
+        const unsigned long long m = lane0_u64(s_marks[wv][word]);
+        const uint32_t rank = nseen + (uint32_t)__popcll(m & (below | (1ull << lane))) - 1u;
+        const uint2 desc = s_ring[wv][rank % kPoolRing];
+        on = (uint32_t)lane < avail;
+        oa = desc.x;
+        od = (desc.y >> 11) & 127u;
+        grp = (oa >> 2) + ((cons + (uint32_t)lane - desc.y) % 2048u);  // a waiting group is less than 2048 behind its node's first
+        orow = (int)(desc.y >> 18);
+        nseen += (uint32_t)__popcll(m);
+        if (lane == 0) s_marks[wv][word] = 0ull;
+        cons += kWave;
+        if (avail < (uint32_t)kWave) prod = cons;  // the line starts afresh at a multiple of 64
+      }
+      worked = true;
+      const int os = wv * NS + (orow & (NS - 1));
+      int32_t sv[4] = {0, 0, 0, 0};
+      bool live[4] = {false, false, false, false};
+      if (on) {
+        const int4 s4 = reinterpret_cast<const int4*>(g.src)[grp];
+        uint4 t4 = make_uint4(0u, 0u, 0u, 0u);
+        if (!WC) t4 = reinterpret_cast<const uint4*>(g.thr)[grp];
+        SetStream st;
+        st.phase_bits = a.phase << 24;
+        st.s_lo = first_lo + s_rel[os];
+        st.s_hi = first_hi + (st.s_lo < first_lo ? 1u : 0u);
+        const uint4 c = draw(key, st, kKindCoin, (uint64_t)grp);
+        sv[0] = s4.x;
+        sv[1] = s4.y;
+        sv[2] = s4.z;
+        sv[3] = s4.w;
+        const uint32_t cv[4] = {c.x, c.y, c.z, c.w};
+        const uint32_t tv[4] = {t4.x, t4.y, t4.z, t4.w};
+        const uint32_t e0 = grp << 2;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) live[w] = e0 + (uint32_t)w - oa < od && edge_live<WC>(cv[w], tv[w], od);
+      }
+      // Every live source sets its signature bit with an atomic OR.  One that
+      // finds the bit clear is new (every queued node's bit is set, and of
+      // several sources sharing a bit only the first sees it clear) and is
+      // appended at once; the others are looked up in the queue after that.
+      bool fast[4];
+      uint32_t nfast = 0, pos = 0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        fast[w] = false;
+        if (live[w]) {
+          const uint32_t hv = sig_hash(sv[w]), b = 1u << ((hv >> (27 - kPoolSigLog)) & 31u);
+          fast[w] = (atomicOr(&s_sig[os][hv >> (32 - kPoolSigLog)], b) & b) == 0u;
+        }
+        nfast += fast[w] ? 1u : 0u;
+      }
+      if (nfast) pos = atomicAdd(&s_tail[os], nfast);
+      wave_sync();
+      // Sets that reach into a block they do not have get one before the
+      // appends: by at most Q nodes of one step, so from one to four blocks.
+      auto grow = [&]() {
+        const uint32_t tail = s_tail[seg];
+        const uint32_t need = has && tail <= (uint32_t)Q ? (tail - 1u) / B : 0u;
+        uint64_t gm = __ballot(is_leader && need > nblk);
+        if (!gm) return;
+        while (gm) {
+          const int src = __ffsll((unsigned long long)gm) - 1;
+          gm &= gm - 1ull;
+          const uint32_t want = (uint32_t)__builtin_amdgcn_readlane((int)need, src);
+          uint32_t have = (uint32_t)__builtin_amdgcn_readlane((int)nblk, src);
+          uint32_t t = have ? (uint32_t)__builtin_amdgcn_readlane((int)tab, src) : 0u;
+          while (have < want && free_blocks) {
+            const uint32_t b = (uint32_t)__ffs((int)free_blocks) - 1u;
+            free_blocks &= free_blocks - 1u;
+            t |= b << (8u * have);
+            ++have;
+          }
+          if (leader == src) {
+            tab = t;
+            nblk = have;
+            if (is_leader) {
+              s_tab[seg] = t;
+              if (have < want) s_tail[seg] = tail + kPoolOver;  // deferred: its appends are dropped
+            }
+          }
+        }
+        wave_sync();
+      };
+      grow();
+      if (nfast) {
+        const bool room = s_tail[os] <= (uint32_t)Q;  // else the set is deferred, and may lack blocks
+        const uint32_t blocks = s_tab[os];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          if (!fast[w]) continue;
+          if (room) nodes[place(orow, blocks, pos)] = sv[w];
+          ++pos;
+          if (MODE == kModeCover && in_seed(a.seed_bits, sv[w])) s_hit[os] = 1u;
+        }
+      }
+      wave_sync();
+      uint64_t m[4];
+#pragma unroll
+      for (int w = 0; w < 4; ++w) m[w] = __ballot(live[w] && !fast[w]);
+      while (m[0] | m[1] | m[2] | m[3]) {
+        const int w = m[0] ? 0 : m[1] ? 1 : m[2] ? 2 : 3;
+        const uint64_t mw = m[0] ? m[0] : m[1] ? m[1] : m[2] ? m[2] : m[3];
+        const int src = __ffsll((unsigned long long)mw) - 1;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) m[i] = i == w ? mw & (mw - 1ull) : m[i];
+        const int32_t u = __builtin_amdgcn_readlane(w == 0 ? sv[0] : w == 1 ? sv[1] : w == 2 ? sv[2] : sv[3], src);
+        const int row = __builtin_amdgcn_readlane(orow, src);
+        const uint32_t tail = s_tail[wv * NS + row];
+        if (tail > (uint32_t)Q) continue;  // outgrown: deferred whatever this source is
+        const uint32_t blocks = s_tab[wv * NS + row];
+        bool found = false;
+        for (uint32_t i = (uint32_t)lane; i < tail; i += kWave) found |= nodes[place(row, blocks, i)] == u;
+        if (__ballot(found) == 0ull) {
+          if (lane == 0) s_tail[wv * NS + row] = tail + 1u;
+          wave_sync();
+          grow();
+          if (lane == 0) {
+            if (s_tail[wv * NS + row] <= (uint32_t)Q) nodes[place(row, s_tab[wv * NS + row], tail)] = u;
+            if (MODE == kModeCover && in_seed(a.seed_bits, u)) s_hit[wv * NS + row] = 1u;
+          }
+          wave_sync();
+        }
+      }
+    }
+    wave_sync();
+  }
+  flush_acc(a, blk, acc, io.acc, lane);
+}
+
+template <int MODE, bool WC>
+__global__ __launch_bounds__(kSegThreads) __attribute__((amdgpu_waves_per_eu(5, 8))) void ic_pool_kernel(SampleArgs a, TierIO io) {
+  __shared__ BlockAcc blk;
+  block_acc_init(blk);
+  ic_pool_run<MODE, WC, true>(a, io, &blk);
 }
 
 // Exact sum of kappa(R) * 2^53 over the widths a width-mode launch wrote
@@ -1866,6 +2266,20 @@ __global__ __launch_bounds__(kSegThreads) void ic_seg_batch_kernel(JobTable t, i
 }
 
 template <int MODE, bool WC>
+__global__ __launch_bounds__(kSegThreads) void ic_pool_batch_kernel(JobTable t, int tier) {
+  const int lane = threadIdx.x % kWave;
+  const int wave = blockIdx.x * (kSegThreads / kWave) + threadIdx.x / kWave;
+  int from = home_job<0>(t, tier, (unsigned long long)wave, (unsigned long long)gridDim.x * (kSegThreads / kWave), lane);
+  for (;;) {
+    const int j = __builtin_amdgcn_readfirstlane(next_job(jobs_with_work<0>(t, tier, lane), from));
+    if (j < 0) break;
+    const SampleArgs& a = t.jobs[j];
+    ic_pool_run<MODE, WC, false>(a, tier_io<0>(a, tier), nullptr);
+    from = j + 1;
+  }
+}
+
+template <int MODE, bool WC>
 __global__ __launch_bounds__(kBigThreads) void ic_big_batch_kernel(JobTable t) {
   __shared__ int s_job;
   int from = blockIdx.x % t.njobs;
@@ -2014,11 +2428,11 @@ int blocks_per_cu(K kernel, int threads) {
   return nb;
 }
 
-// Tier-0 shapes: S lanes per set, a queue of Q nodes per set in LDS (with a
-// hash of 2^HLOG slots for S >= 16), and at most GMAX 4-edge groups per set
-// so that wide sets, which hold a hub's long in-list, move on to a tier with
-// more lanes per set instead of forming a long tail.  The hash-free shapes
-// keep 16 KB of LDS per block, so a CU holds 32 wavefronts.
+// Tier-0 shapes.  8 (the default): sixteen sets per wavefront (ic_pool_run).
+// Others: S lanes per set, a queue of Q nodes per set in LDS (with a hash of
+// 2^HLOG slots for S >= 16), and at most GMAX 4-edge groups per set so that wide
+// sets, which hold a hub's long in-list, move on to a tier with more lanes per
+// set instead of forming a long tail.
 template <int MODE, bool WC, int S>
 struct SegKernel;
 template <int MODE, bool WC>
@@ -2027,7 +2441,7 @@ struct SegKernel<MODE, WC, 4> {
 };
 template <int MODE, bool WC>
 struct SegKernel<MODE, WC, 8> {
-  static constexpr auto fn = ic_seg_kernel<MODE, WC, 8, 128, 0, 512, kSegGroups>;
+  static constexpr auto fn = ic_pool_kernel<MODE, WC>;
 };
 template <int MODE, bool WC>
 struct SegKernel<MODE, WC, 16> {
@@ -2041,7 +2455,6 @@ template <int MODE, bool WC>
 struct SegKernel<MODE, WC, 64> {
   static constexpr auto fn = ic_seg_kernel<MODE, WC, 64, 512, 10, 2048, kSegGroups>;
 };
-// tier 1: one set per wavefront
 template <int MODE, bool WC>
 struct Tier1Kernel {
   static constexpr auto fn = ic_seg_kernel<MODE, WC, 64, 512, 10, 64 * 64, kSegGroups>;
@@ -2094,10 +2507,10 @@ void launch_lt(const SampleArgs& a, int grid0, int grid2, hipStream_t s, hipEven
   if (MODE == kModeWidth || (MODE == kModeEmit && a.wbuf)) launch_kappa_reduce(a, s);
 }
 
-// Batched launches: 8 lanes per set in tier 0, as SegKernel<., ., 8>.
+// Batched launches: the default shape in tier 0, as SegKernel<., ., 8>.
 template <int MODE, bool WC>
 struct BatchKernels {
-  static constexpr auto seg0 = ic_seg_batch_kernel<MODE, WC, 8, 128, 0, 512, kSegGroups>;
+  static constexpr auto seg0 = ic_pool_batch_kernel<MODE, WC>;
   static constexpr auto seg1 = ic_seg_batch_kernel<MODE, WC, 64, 512, 10, 64 * 64, kSegGroups>;
 };
 
@@ -2208,7 +2621,7 @@ uint32_t tier0_set_cap(int model, int seg_lanes) {
   if (model == 2) return (uint32_t)kTrigSegQ;
   switch (seg_lanes) {
     case 4: return 64;
-    case 8: return 128;
+    case 8: return (uint32_t)kPoolQ;
     case 16: return 128;
     case 32: return 256;
     default: return 512;
