@@ -1998,7 +1998,8 @@ enum ChainPhase : int {
   kTortoise = 2, // tortoise and hare step together until they meet (mu)
   kHare = 3,
   kWalk = 4,     // output walk over the mu + lambda nodes
-  kIdle = 5
+  kIdle = 5,
+  kHash = 6      // walk marking its nodes in the lane's LDS table
 };
 
 // f(v) and indeg(v): the in-neighbour the walk moves to from v, or -1 where
@@ -2014,25 +2015,46 @@ __device__ __forceinline__ int32_t lt_next(const GraphView& g, const Key& key, c
 
 constexpr int kChainWaves = 4;  // wavefronts per block of the long-chain tier
 
-template <int MODE>
+// The search costs about five steps of f per node, each a chain of dependent
+// loads, and few chains outgrow the first tier (0.03 to 0.13% of the LT sets on
+// graphs of 100K to 1M nodes; none had more than 120 nodes), so the launch lasts
+// as long as one of them.  A launch of at most kLtHashMost such chains therefore
+// walks them once, marking the nodes in an LDS table per lane, with few chains
+// per wavefront; a chain of kLtHashCap nodes goes on with the search.  With 64 KB
+// of tables per wavefront only two fit a CU: longer lists keep to the search,
+// which fills the chip.  LT with in-weights on the 1M-node graph: 753 to 885 us
+// per launch by the search, 160 us with tables (TIM+ with k = 10: 8.2 -> 5.7 ms).
+constexpr int kLtHashLog = 8;
+constexpr uint32_t kLtHashCap = 192;
+constexpr int kLtHashBlocks = 512;  // one wavefront each, two per CU
+constexpr unsigned long long kLtHashMost = (unsigned long long)kLtHashBlocks * kWave;
+
+template <int MODE, bool HASH>
 __device__ __forceinline__ void lt_chain_run(const SampleArgs& a, const TierIO& io, bool first_only,
                                              BlockAcc* blk = nullptr) {
+  constexpr int NW = HASH ? 1 : kChainWaves, SLOTS = 1 << kLtHashLog;
+  __shared__ uint32_t s_tab[HASH ? kWave : 1][HASH ? SLOTS + 1 : 1];  // (a word more: rows start in different banks)
   const int lane = threadIdx.x % kWave;
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
   const GraphView g = a.g;
   const Key key = make_key(a.seed);
   const unsigned long long total = list_len(a, io.in_len_ctr);
-  if (first_only) {  // a chain per lane to start with: later wavefronts are not needed
-    const unsigned long long wave = (unsigned long long)blockIdx.x * kChainWaves + threadIdx.x / kWave;
-    if (wave * (unsigned long long)kWave >= total) {
+  if (first_only) {  // a chain per lane to start with (tables: per wavefront): later wavefronts are not needed
+    const unsigned long long wave = (unsigned long long)blockIdx.x * NW + threadIdx.x / kWave;
+    if (wave * (unsigned long long)(HASH ? 1 : kWave) >= total || (HASH && total > kLtHashMost)) {
       flush_acc(a, blk, Acc(), io.acc, lane);
       return;
     }
   }
   Acc acc;
   Reservoir res;
-  res.chunk = chunk_for(total, kChainWaves, kWave);
   bool exhausted = false;
+  if (HASH) {
+    res.chunk = (total + gridDim.x - 1) / gridDim.x;
+    exhausted = (unsigned long long)lane >= res.chunk;  // lanes beyond stay idle: the chains spread over the wavefronts
+  } else {
+    res.chunk = chunk_for(total, kChainWaves, kWave);
+  }
   int phase = kIdle;
   unsigned long long rel = 0, width = 0, base = 0;
   SetStream st = make_set_stream(a.phase, a.first);
@@ -2041,14 +2063,28 @@ __device__ __forceinline__ void lt_chain_run(const SampleArgs& a, const TierIO& 
   for (;;) {
     {
       unsigned long long item = 0;
-      if (take(a, io.next_ctr, 1, total, res, phase == kIdle && !exhausted, true, below, lane, exhausted, item)) {
+      const bool got = take(a, io.next_ctr, 1, total, res, phase == kIdle && !exhausted, true, below, lane, exhausted, item);
+      if (HASH) {
+        uint64_t m = __ballot(got);
+        while (m) {
+          const int row = __ffsll((unsigned long long)m) - 1;
+          m &= m - 1ull;
+          for (int i = lane; i < SLOTS; i += kWave) s_tab[row][i] = 0u;
+        }
+        wave_sync();
+      }
+      if (got) {
         rel = io.in_list[item];
         st = make_set_stream(a.phase, a.first + rel);
         x0 = draw_root(key, st, g.n);
         cur = x0;
         pos = 0;
         width = 0;
-        phase = kSearch;
+        phase = HASH ? kHash : kSearch;
+        if (HASH) {
+          len = 1;
+          lds_insert<kLtHashLog>(s_tab[HASH ? lane : 0], (uint32_t)x0);
+        }
         if (MODE == kModeCover && in_seed(a.seed_bits, x0)) {
           acc.covered += 1;
           phase = kIdle;
@@ -2056,99 +2092,145 @@ __device__ __forceinline__ void lt_chain_run(const SampleArgs& a, const TierIO& 
       }
     }
     if (__ballot(phase != kIdle) == 0) break;
-    if (phase == kIdle) continue;
-    const int ph = phase;  // this iteration's step is f(cur) of phase ph
-    int64_t d = 0;
-    const int32_t nx = lt_next(g, key, st, cur, d);
-    bool done = false, walk = false;
-    if (ph == kSearch) {
-      // cur is the hare, at position pos
-      if (nx < 0) {  // x_pos has no in-edges: the set is x_0 .. x_pos
-        len = pos + 1;
-        if (MODE == kModeCover) done = true;
-        else walk = true;
-      } else {
-        if (pos == 0) {
-          tort = x0;
-          power = 1;
-          lam = 1;
-        } else {
-          if (power == lam) {
-            tort = cur;
-            power <<= 1;
-            lam = 0;
-          }
-          ++lam;
-        }
-        ++pos;
-        cur = nx;
-        if (MODE == kModeCover && in_seed(a.seed_bits, nx)) {
-          acc.covered += 1;
-          done = true;
-        } else if (nx == tort) {  // a cycle of length lam; the hare has passed every node of the set
-          if (MODE == kModeCover) {
+    bool marked = false;  // the table walk is done: the set's nodes are the table's
+    if (phase != kIdle) {
+      const int ph = phase;  // this iteration's step is f(cur) of phase ph
+      int64_t d = 0;
+      const int32_t nx = lt_next(g, key, st, cur, d);
+      bool done = false, walk = false;
+      if (HASH && ph == kHash) {
+        width += (unsigned long long)d;
+        marked = nx < 0 || lds_insert<kLtHashLog>(s_tab[HASH ? lane : 0], (uint32_t)nx) == 0;
+        if (!marked) {
+          ++len;
+          cur = nx;
+          if (MODE == kModeCover && in_seed(a.seed_bits, nx)) {
+            acc.covered += 1;
             done = true;
-          } else {
-            phase = kAdvance;
-            cnt = 0;
+          } else if (len == kLtHashCap) {
+            phase = kSearch;
             cur = x0;
+            width = 0;
+          }
+        } else if (MODE != kModeEmit) {
+          done = true;
+        }
+      } else if (ph == kSearch) {
+        // cur is the hare, at position pos
+        if (nx < 0) {  // x_pos has no in-edges: the set is x_0 .. x_pos
+          len = pos + 1;
+          if (MODE == kModeCover) done = true;
+          else walk = true;
+        } else {
+          if (pos == 0) {
+            tort = x0;
+            power = 1;
+            lam = 1;
+          } else {
+            if (power == lam) {
+              tort = cur;
+              power <<= 1;
+              lam = 0;
+            }
+            ++lam;
+          }
+          ++pos;
+          cur = nx;
+          if (MODE == kModeCover && in_seed(a.seed_bits, nx)) {
+            acc.covered += 1;
+            done = true;
+          } else if (nx == tort) {  // a cycle of length lam; the hare has passed every node of the set
+            if (MODE == kModeCover) {
+              done = true;
+            } else {
+              phase = kAdvance;
+              cnt = 0;
+              cur = x0;
+            }
           }
         }
-      }
-    } else if (ph == kAdvance) {  // hare = x_cnt
-      cur = nx;
-      if (++cnt == lam) {
+      } else if (ph == kAdvance) {  // hare = x_cnt
+        cur = nx;
+        if (++cnt == lam) {
+          hare = nx;
+          tort = x0;
+          mu = 0;
+          if (tort == hare) {
+            len = lam;
+            walk = true;
+          } else {
+            phase = kTortoise;
+            cur = tort;
+          }
+        }
+      } else if (ph == kTortoise) {
+        tort = nx;
+        phase = kHare;
+        cur = hare;
+      } else if (ph == kHare) {
         hare = nx;
-        tort = x0;
-        mu = 0;
+        ++mu;
         if (tort == hare) {
-          len = lam;
+          len = mu + lam;
           walk = true;
         } else {
           phase = kTortoise;
           cur = tort;
         }
+      } else {  // kWalk: cur = x_pos, with indeg d and successor nx
+        width += (unsigned long long)d;
+        if (MODE == kModeEmit && base + len <= a.pool_cap) a.pool[base + pos] = cur;
+        if (++pos == len) done = true;
+        else cur = nx;
       }
-    } else if (ph == kTortoise) {
-      tort = nx;
-      phase = kHare;
-      cur = hare;
-    } else if (ph == kHare) {
-      hare = nx;
-      ++mu;
-      if (tort == hare) {
-        len = mu + lam;
-        walk = true;
-      } else {
-        phase = kTortoise;
-        cur = tort;
+      if (walk) {
+        phase = kWalk;
+        cur = x0;
+        pos = 0;
+        if (MODE == kModeEmit) base = atomicAdd(&a.ctr[kCtrPoolCursor], (unsigned long long)len);
       }
-    } else {  // kWalk: cur = x_pos, with indeg d and successor nx
-      width += (unsigned long long)d;
-      if (MODE == kModeEmit && base + len <= a.pool_cap) a.pool[base + pos] = cur;
-      if (++pos == len) done = true;
-      else cur = nx;
+      if (done) {
+        phase = kIdle;
+        if (MODE == kModeWidth) {
+          a.wbuf[rel] = (uint32_t)width;
+          acc.width += width;
+          acc.nodes += len;
+          if (a.sizes) a.sizes[rel] = len;
+        } else if (MODE == kModeEmit) {
+          a.set_start[rel] = a.pool_base + base;
+          a.set_len[rel] = len;
+          if (a.widths) a.widths[rel] = width;
+          if (a.wbuf) a.wbuf[rel] = (uint32_t)width;
+          acc.width += width;
+          acc.nodes += len;
+        }
+      }
     }
-    if (walk) {
-      phase = kWalk;
-      cur = x0;
-      pos = 0;
-      if (MODE == kModeEmit) base = atomicAdd(&a.ctr[kCtrPoolCursor], (unsigned long long)len);
-    }
-    if (done) {
-      phase = kIdle;
-      if (MODE == kModeWidth) {
-        a.wbuf[rel] = (uint32_t)width;
-        acc.width += width;
-        acc.nodes += len;
-        if (a.sizes) a.sizes[rel] = len;
-      } else if (MODE == kModeEmit) {
-        a.set_start[rel] = a.pool_base + base;
-        a.set_len[rel] = len;
-        if (a.widths) a.widths[rel] = width;
-        if (a.wbuf) a.wbuf[rel] = (uint32_t)width;
-        acc.width += width;
-        acc.nodes += len;
+    if (HASH && MODE == kModeEmit) {
+      uint64_t m = __ballot(marked);
+      while (m) {  // the wavefront copies the table's nodes
+        const int row = __ffsll((unsigned long long)m) - 1;
+        m &= m - 1ull;
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)len, row);
+        unsigned long long at = 0;
+        if (lane == 0) at = atomicAdd(&a.ctr[kCtrPoolCursor], (unsigned long long)n);
+        at = lane0_u64(at);
+        uint32_t out = 0;
+        for (int i = lane; i < SLOTS; i += kWave) {
+          const uint32_t k = s_tab[HASH ? row : 0][HASH ? i : 0];
+          const uint64_t km = __ballot(k != 0u);
+          if (k && at + n <= a.pool_cap) a.pool[at + out + (uint32_t)__popcll(km & below)] = (int32_t)(k - 1u);
+          out += (uint32_t)__popcll(km);
+        }
+        if (lane == row) {
+          a.set_start[rel] = a.pool_base + at;
+          a.set_len[rel] = n;
+          if (a.widths) a.widths[rel] = width;
+          if (a.wbuf) a.wbuf[rel] = (uint32_t)width;
+          acc.width += width;
+          acc.nodes += n;
+          phase = kIdle;
+        }
       }
     }
   }
@@ -2156,10 +2238,17 @@ __device__ __forceinline__ void lt_chain_run(const SampleArgs& a, const TierIO& 
 }
 
 template <int MODE>
+__global__ __launch_bounds__(kWave) void lt_hash_kernel(SampleArgs a, TierIO io) {
+  lt_chain_run<MODE, true>(a, io, true);
+}
+
+// Takes what lt_hash_kernel has left (nothing, where that kernel ran).
+template <int MODE>
 __global__ __launch_bounds__(kChainWaves* kWave) void lt_chain_kernel(SampleArgs a, TierIO io) {
+  if (a.ctr[io.next_ctr] >= list_len(a, io.in_len_ctr)) return;
   __shared__ BlockAcc blk;
   block_acc_init(blk);
-  lt_chain_run<MODE>(a, io, true, &blk);
+  lt_chain_run<MODE, false>(a, io, true, &blk);
 }
 
 __global__ void clear_counters_kernel(unsigned long long* ctr) {
@@ -2312,6 +2401,28 @@ __global__ __launch_bounds__(kLtWaves* kWave) void lt_lane_batch_kernel(JobTable
   }
 }
 
+// The table walk of lt_chain_run where the jobs' long chains together fill
+// its wavefronts at most.
+template <int MODE>
+__global__ __launch_bounds__(kWave) void lt_hash_batch_kernel(JobTable t) {
+  const int lane = threadIdx.x % kWave;
+  unsigned long long c = 0;
+  if (lane < t.njobs) {
+    const SampleArgs* a = t.jobs + lane;
+    const unsigned long long d = load_ctr(a->ctr + kCtrList1);
+    c = d < a->count ? d : a->count;
+  }
+  if (seg_sum<kWave>(c) > kLtHashMost) return;
+  int from = home_job<1>(t, 2, (unsigned long long)blockIdx.x, (unsigned long long)gridDim.x, lane);
+  for (;;) {
+    const int j = __builtin_amdgcn_readfirstlane(next_job(jobs_with_work<1>(t, 2, lane), from));
+    if (j < 0) break;
+    const SampleArgs& a = t.jobs[j];
+    lt_chain_run<MODE, true>(a, tier_io<1>(a, 2), false);
+    from = j + 1;
+  }
+}
+
 template <int MODE>
 __global__ __launch_bounds__(kChainWaves* kWave) void lt_chain_batch_kernel(JobTable t) {
   const int lane = threadIdx.x % kWave;
@@ -2321,7 +2432,7 @@ __global__ __launch_bounds__(kChainWaves* kWave) void lt_chain_batch_kernel(JobT
     const int j = __builtin_amdgcn_readfirstlane(next_job(jobs_with_work<1>(t, 2, lane), from));
     if (j < 0) break;
     const SampleArgs& a = t.jobs[j];
-    lt_chain_run<MODE>(a, tier_io<1>(a, 2), false);
+    lt_chain_run<MODE, false>(a, tier_io<1>(a, 2), false);
     from = j + 1;
   }
 }
@@ -2503,6 +2614,7 @@ void launch_lt(const SampleArgs& a, int grid0, int grid2, hipStream_t s, hipEven
   const TierIO t2 = {a.list1, kCtrList1, kCtrNext2, nullptr, 0, 2, 1};
   hipLaunchKernelGGL((lt_lane_kernel<MODE>), dim3(grid0), dim3(kLtWaves * kWave), 0, s, a, t0);
   if (after0) (void)hipEventRecord(after0, s);
+  hipLaunchKernelGGL((lt_hash_kernel<MODE>), dim3(kLtHashBlocks), dim3(kWave), 0, s, a, t2);
   hipLaunchKernelGGL((lt_chain_kernel<MODE>), dim3(grid2), dim3(kChainWaves * kWave), 0, s, a, t2);
   if (MODE == kModeWidth || (MODE == kModeEmit && a.wbuf)) launch_kappa_reduce(a, s);
 }
@@ -2530,6 +2642,7 @@ template <int MODE>
 void launch_lt_batch(const JobTable& t, int grid0, int grid2, unsigned kappa_blocks, hipStream_t s, hipEvent_t after0) {
   hipLaunchKernelGGL((lt_lane_batch_kernel<MODE>), dim3(grid0), dim3(kLtWaves * kWave), 0, s, t);
   if (after0) (void)hipEventRecord(after0, s);
+  hipLaunchKernelGGL((lt_hash_batch_kernel<MODE>), dim3(kLtHashBlocks), dim3(kWave), 0, s, t);
   hipLaunchKernelGGL((lt_chain_batch_kernel<MODE>), dim3(grid2), dim3(kChainWaves * kWave), 0, s, t);
   if (MODE == kModeWidth || MODE == kModeEmit)
     hipLaunchKernelGGL(kappa_reduce_batch_kernel, dim3(kappa_blocks, t.njobs), dim3(kSegThreads), 0, s, t,
