@@ -2266,8 +2266,10 @@ tim_status tim_graph_set_lt_weights(tim_ctx* c, tim_graph* g, const uint32_t* lt
       if (lt_thr[e] < lt_thr[e - 1])
         return fail(TIM_EINVAL, "LT thresholds of node %lld decrease at edge %lld", (long long)v, (long long)e);
   uint32_t* d = nullptr;
-  if (hipMalloc(&d, (size_t)g->m * 4) != hipSuccess) return fail(TIM_ENOMEM, "LT thresholds: hipMalloc failed");
-  if (hipMemcpyAsync(d, lt_thr, (size_t)g->m * 4, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
+  // four words of padding: the pick reads four thresholds at a time
+  if (hipMalloc(&d, (size_t)g->m * 4 + 16) != hipSuccess) return fail(TIM_ENOMEM, "LT thresholds: hipMalloc failed");
+  if (hipMemsetAsync(d + g->m, 0xFF, 16, c->stream) != hipSuccess ||
+      hipMemcpyAsync(d, lt_thr, (size_t)g->m * 4, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess) {
     (void)hipFree(d);
     return fail(TIM_EDEVICE, "LT thresholds: copy failed");

@@ -69,7 +69,7 @@ struct GraphView {
   const uint32_t* off32;  // the same offsets in 32 bits (m < 2^32), for the IC first tiers
   const int32_t* src;   // m rounded up to a multiple of 4, plus 4, zero padded
   const uint32_t* thr;  // same padding, or nullptr for the weighted cascade
-  const uint32_t* lthr; // LT cumulative in-weight thresholds (m), or nullptr for 1/indeg
+  const uint32_t* lthr; // LT cumulative in-weight thresholds (m, and four words of padding), or nullptr for 1/indeg
   // general triggering model: outcomes of v are [toff[v], toff[v+1]) with
   // cumulative thresholds tthr; outcome j's members (local in-edge indices)
   // are tmem[tset[j] .. tset[j+1])

@@ -1321,8 +1321,8 @@ __device__ __forceinline__ void lt_lane_run(const SampleArgs& a, const TierIO& i
     if (active) {
       done = hit;
       if (!done) {
-        const int64_t ea = g.off[v];
-        const int64_t d = g.off[v + 1] - ea;
+        const int64_t ea = g.off32[v];  // with off32[v + 1]: one 8-byte load
+        const int64_t d = (int64_t)g.off32[v + 1] - ea;
         width += (unsigned long long)d;
         const int64_t e = d ? lt_pick_edge(g, key, st, v, ea, d) : -1;
         if (e < 0) {
@@ -2006,8 +2006,8 @@ enum ChainPhase : int {
 // the walk stops (no in-edges, or the empty triggering set).
 __device__ __forceinline__ int32_t lt_next(const GraphView& g, const Key& key, const SetStream& st, int32_t v,
                                            int64_t& d) {
-  const int64_t ea = g.off[v];
-  d = g.off[v + 1] - ea;
+  const int64_t ea = g.off32[v];
+  d = (int64_t)g.off32[v + 1] - ea;
   if (d == 0) return -1;
   const int64_t e = lt_pick_edge(g, key, st, v, ea, d);
   return e < 0 ? -1 : g.src[e];

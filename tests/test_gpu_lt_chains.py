@@ -65,3 +65,31 @@ def test_lists_around_the_table_walks_limit(eng, count):
     x = nodes.cpu().numpy().reshape(count, 70)
     assert np.array_equal(np.sort(x, axis=1) % 70, np.tile(np.arange(70), (count, 1)))
     eng.free(dg)
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 4, 5, 7, 8, 9, 64, 1000, 20000])
+@pytest.mark.parametrize("kind", ["random", "half", "steps", "one", "equal"])
+def test_weighted_pick_at_hubs(eng, d, kind):
+    """Hubs of in-degree d over leaves whose only in-neighbour is a hub; cumulative thresholds from even to extreme."""
+    hubs, leaves = 4, max(d, 8)
+    e = [(hubs + (i * 7 + h) % leaves, h) for h in range(hubs) for i in range(d)]
+    e += [(x % hubs, hubs + x) for x in range(leaves)]
+    g = synth.from_edges(hubs + leaves, sorted(set(e)))
+    r = np.random.default_rng(d)
+    thr = np.empty(g.m, dtype=np.uint32)
+    for v in range(g.n):
+        k = int(g.off[v + 1] - g.off[v])
+        w = {"random": r.random(k) + 1e-3, "half": r.random(k) + 1e-3, "steps": np.where(r.random(k) < 0.05, 1.0, 1e-12),
+             "one": np.eye(1, k, k // 2)[0] + 1e-15, "equal": np.ones(k)}[kind]
+        c = np.cumsum(w) / w.sum() * (0.5 if kind == "half" else 1.0)
+        thr[g.off[v]:g.off[v + 1]] = np.maximum(np.floor(c * 2.0**32) - 1, 0).clip(0, 2**32 - 1).astype(np.uint64)
+    dg = eng.upload(g)
+    eng.set_lt_weights(dg, g, thr)
+    print(f"pick {kind} d={d} m={g.m}", file=sys.stderr, flush=True)
+    count = 3000
+    off, nodes, widths, _ = eng.sample_rr(dg, LT, 5, 3, 0, count)
+    wo, wn, ww = oracle.sample_sets(g, LT, 5, 3, 0, count, thr=thr)
+    assert np.array_equal(off.cpu().numpy(), wo) and np.array_equal(widths.cpu().numpy().astype(np.uint64), ww)
+    sid = np.repeat(np.arange(count, dtype=np.int64), np.diff(wo))
+    assert np.array_equal(np.sort(sid * g.n + nodes.cpu().numpy()), np.sort(sid * g.n + wn))
+    eng.free(dg)
