@@ -704,10 +704,12 @@ tim_status greedy(tim_ctx* c, int64_t n, uint64_t nsets, const int64_t* set_off,
     a.bkt = c->bucket.p;
   a.k = k;
   std::vector<unsigned long long> keys((size_t)k);
-  for (;;) {
+  for (bool again = true; again;) {
     if (c->prof_on) HIP_TRY(hipEventRecord(c->pev[0], c->stream));
-    if (index) tim::launch_index(a, c->stream);
-    else tim::launch_counts(a, c->stream);
+    if (a.launched == 0) {
+      if (index) tim::launch_index(a, c->stream);
+      else tim::launch_counts(a, c->stream);
+    }
     if (c->prof_on) HIP_TRY(hipEventRecord(c->pev[1], c->stream));
     tim::launch_greedy(a, k, c->stream);
     if (c->prof_on) HIP_TRY(hipEventRecord(c->pev[2], c->stream));
@@ -718,13 +720,17 @@ tim_status greedy(tim_ctx* c, int64_t n, uint64_t nsets, const int64_t* set_off,
       float ms_index = 0.f, ms_greedy = 0.f;
       HIP_TRY(hipEventElapsedTime(&ms_index, c->pev[0], c->pev[1]));
       HIP_TRY(hipEventElapsedTime(&ms_greedy, c->pev[1], c->pev[2]));
-      c->prof.index_calls += 1;
+      c->prof.index_calls += a.launched == 0 ? 1 : 0;
       c->prof.index_ms += ms_index;
       c->prof.greedy_ms += ms_greedy;
     }
-    // a key of 0: the candidates of the largest counts did not decide that step; run it over all nodes
-    if (keys[(size_t)k - 1] != 0ull || a.all_nodes) break;
-    a.all_nodes = 1;
+    // keys left 0: more launches over the candidates; a key of 1: they do not decide that step, so over all nodes
+    again = keys[(size_t)k - 1] == 0ull && !a.all_nodes;
+    a.launched += tim::cand_launches(k);
+    if (again && (a.launched >= k + tim::cand_launches(k) || std::find(keys.begin(), keys.end(), 1ull) != keys.end())) {
+      a.all_nodes = 1;
+      a.launched = 0;
+    }
   }
   for (int j = 0; j < k; ++j) {
     seeds[j] = (int32_t)(0xFFFFFFFFull - (keys[j] & 0xFFFFFFFFull));

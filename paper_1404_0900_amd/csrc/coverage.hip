@@ -696,21 +696,31 @@ __global__ __launch_bounds__(kThreads) void scan_cover_kernel(const unsigned lon
 // Counts only fall, so a node whose initial count is below T is never chosen
 // while some candidate (initial count at least T) still has T or more.  The
 // greedy of k > 1 therefore takes the nodes of the largest counts as
-// candidates (kCandPerStep per step, at least kCandMin, at most kCandMax),
+// candidates (kCandPerStep per step, at least kCandMin, at most kCandMax) and
 // keeps of every set only its candidates, as a stream of 16-bit candidate
-// numbers whose top bit marks the first entry of a set, and runs each step as
-// one kernel over the stream: every block finds the best candidate itself,
-// compares its part of the stream with it, and takes the matched sets out of
-// the stream and of the counts.  No inverted index is built, no set offsets or
-// covered marks are kept, and the argmax reads the candidates instead of n
-// nodes.  A step whose best candidate has fallen below T writes key 0, the
-// later steps leave at once, and the caller runs the greedy over all nodes.
-// Seeds and gains are those of that greedy: the step's key is the largest
-// over all nodes (every other node's count is below T).
+// numbers whose top bit marks the first entry of a set.  One kernel over the
+// stream takes one or several greedy steps: every block decides them itself from
+// the counts, then takes the sets of the chosen candidates in its part of the
+// stream out of the stream and of the counts.  No inverted index is built, no
+// set offsets or covered marks are kept, and the argmax reads the candidates
+// instead of n nodes.
+// Several steps at once: each launch also counts, over the sets it leaves, how
+// many contain each combination of kCandTop candidates of large counts (the tops).
+// While the best candidate is one of those, the counts of the others after its
+// choice follow from the combinations, and the best of them is the next choice as
+// long as its key is above that of every candidate outside the tops (their counts
+// only fall).
+// A launch whose best candidate has fallen below T leaves key 1, which no choice
+// has, and the caller runs the greedy over all nodes.  Seeds and gains are those
+// of that greedy: a choice's key is the largest over all nodes at its step.
 // Against the inverted index with an argmax over n nodes and a cover pass per
-// step: TIM+ with k = 50 on the 1M-node graph under IC 5.41 -> 4.67 ms, on 15K
-// nodes under LT 1.78 -> 1.48 ms, with k = 25 on 123K nodes and per-edge
-// probabilities 4.58 -> 3.79 ms.  A step takes 7 to 9 us (10 to 16 before).
+// step (10 to 16 us a step), TIM+ runs took: k = 50 on the 1M-node graph under IC
+// 5.41 -> 4.67 ms with one step per launch (7 to 9 us), k = 50 on 15K nodes under
+// LT 1.78 -> 1.48 ms, k = 25 on 123K nodes with per-edge probabilities 4.58 ->
+// 3.79 ms.  With several steps per launch (13 to 16 launches instead of 50 for
+// k = 50, 4 to 6 instead of 10 for k = 10) k = 50 on the 1M-node graph went 4.20 ->
+// 3.76 ms, k = 50 on 15K nodes under LT 1.56 -> 1.14, k = 25 on 123K nodes 3.42 ->
+// 3.16, k = 20 on 300K stored sets 1.09 -> 1.02, k = 10 on 3K nodes 0.93 -> 0.88.
 // Half the candidates per step (128) leave the triggering model's greedy of
 // k = 10 on 200K nodes undecided (6.1 -> 6.6 ms) and gain nothing elsewhere.
 constexpr int kCandMin = 2048, kCandMax = 8192, kCandPerStep = 256;
@@ -722,16 +732,25 @@ constexpr int kCandBins = 1024;
 constexpr uint32_t kCandBinsUsed = 128u + 25u * 16u;  // those above belong to no 32-bit count
 constexpr int kCandSegs = 256;       // parts of the stream, one per block of a step
 constexpr int kCandStepThreads = 1024;
-constexpr int kCandHits = 576;       // matched entries a wavefront holds before it takes their sets out
 constexpr int kCandBuildThreads = 1024;
 constexpr int kCandTileMax = kCandBuildThreads;  // sets per tile of the build, one per thread
 constexpr int kCandWindow = 4096;    // entries per window of the build
+constexpr int kCandTop = 8;          // tops whose combinations are counted
+constexpr int kCandCombos = 1 << kCandTop;
+constexpr int kCandRows = 8;         // counters per combination: blocks add to that of their number mod 8
+constexpr int kCandTileVecs = 4;     // vectors of eight entries per thread in a tile of the stream
+constexpr uint32_t kCandChosen = 0x100u;  // class bit of this launch's choices (below it: one bit per top)
+constexpr uint32_t kCandOpen = 0x200u;    // with them: the set goes on after the tile
+constexpr uint32_t kCandStarts = 1u << 24;
 
 struct CandHead {  // counters of one greedy
   uint32_t n;      // candidates
   uint32_t t;      // T
   uint32_t cursor; // stream entries reserved
   uint32_t failed; // a step found no candidate at or above T
+  uint32_t picked[2];  // choices before launches j mod 2
+  uint32_t tops[2][kCandTop];  // number + 1 of the tops counted by launch j - 1 (0: none), for launches j mod 2
+  alignas(16) uint32_t combos[3][kCandRows][kCandCombos];  // sets left with each combination by launches j mod 3
 };
 
 struct CandArrays {
@@ -761,9 +780,10 @@ __device__ __forceinline__ uint32_t cand_bin_low(uint32_t b) {
 
 // Clears the counters, bins and dec, and marks every candidate number of
 // base as taken until cand_pick_kernel gives it to a node.
-__global__ void cand_init_kernel(CandArrays c) {
+__global__ void cand_init_kernel(CandArrays c, unsigned long long* best, int k) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
-  if (i == 0) *c.head = CandHead{0u, 0u, 0u, 0u};
+  for (int x = i; x < (int)(sizeof(CandHead) / 4); x += stride) reinterpret_cast<uint32_t*>(c.head)[x] = 0u;
+  for (int x = i; x < k; x += stride) best[x] = 0ull;
   for (int x = i; x < kCandBins; x += stride) c.bins[x] = 0u;
   for (int x = i; x < 3 * kCandMax; x += stride) c.dec[x] = 0u;
   for (int x = i; x < 2 * kCandMax; x += stride) c.base[x] = kCandTaken;
@@ -957,221 +977,479 @@ __global__ __launch_bounds__(kCandBuildThreads) void cand_build_kernel(V sets, u
   }
 }
 
-// The largest (smallest) value of eight neighbouring lanes, in all of them.
-__device__ __forceinline__ int max8(int x) {
-#pragma unroll
-  for (int o = 1; o < 8; o <<= 1) x = max(x, __shfl_xor(x, o, 64));
-  return x;
-}
-__device__ __forceinline__ int min8(int x) {
-#pragma unroll
-  for (int o = 1; o < 8; o <<= 1) x = min(x, __shfl_xor(x, o, 64));
-  return x;
+// x of the lane that DPP control CTRL names.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp32(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
 }
 
-// Takes the sets of the matched entries hits[0, nh) out of a part of the
-// stream: eight lanes per set, which read the 64-entry window (one 128-byte
-// line) of the match, go back until the set's first entry and forward until
-// the next set's, counting every entry in dec and overwriting it.  Sets keep
-// the marks of their first entries, and no two matches lie in one set, so
-// neighbouring sets may be taken out at the same time.
-__device__ __forceinline__ void cand_take_out(uint16_t* part, int nwin, const uint32_t* hits, int nh, uint32_t* dec,
-                                              int lane) {
-  const int gl = lane & 7;
-  const uint4* vec = reinterpret_cast<const uint4*>(part);
-  for (int h0 = 0; h0 < nh; h0 += 8) {
-    const int h = h0 + (lane >> 3);
-    bool active = h < nh;
-    const int p = active ? (int)hits[h] : 0;
-    int w = p >> 6, start = -1;
-    uint4 x = make_uint4(0u, 0u, 0u, 0u);
-    bool back = active;
-    while (__ballot(back)) {
-      if (back) x = vec[w * 8 + gl];
-      const uint32_t word[4] = {x.x, x.y, x.z, x.w};
-      int mine = -1;
-      const int pos0 = w * 64 + gl * 8;
+template <int CTRL>
+__device__ __forceinline__ unsigned long long dpp64(unsigned long long x) {
+  return ((unsigned long long)dpp32<CTRL>((uint32_t)(x >> 32)) << 32) | dpp32<CTRL>((uint32_t)x);
+}
+
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141;  // quad_perm [1,0,3,2], [2,3,0,1]
+constexpr int kDppRowShr = 0x110, kDppRowRor = 0x120;                    // + 1..15
+
+// Sum over eight neighbouring lanes, in all of them (every lane of the wavefront active).
+__device__ __forceinline__ uint32_t sum8(uint32_t x) {
+  x += dpp32<kDppXor1>(x);
+  x += dpp32<kDppXor2>(x);
+  return x + dpp32<kDppHalfMirror>(x);
+}
+
+// The lanes are consecutive pieces of the stream: with `starts` sets start in the
+// piece, head are the classes before the first of them and tail those from the
+// last on; without, head are its classes.  to_end: classes of the set open at the
+// lane's end, from its start or lane 0 on; on: classes from the lane's first entry
+// up to the next set's start or the end of lane 63.
+__device__ __forceinline__ void scan_classes(uint32_t head, uint32_t tail, bool starts, int lane, uint32_t* to_end,
+                                             uint32_t* on) {
+  const uint64_t all = __ballot(starts), upto = all & (~0ull >> (63 - lane)), from = all & (~0ull << lane);
+  const int back = upto ? lane - (63 - __clzll((long long)upto)) : lane;
+  const int ahead = from ? __ffsll((unsigned long long)from) - 1 - lane : 63 - lane;
+  uint32_t p = starts ? tail : head, q = head;
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (((word[i >> 1] >> (16 * (i & 1))) & kCandFirst) && pos0 + i <= p) mine = pos0 + i;
-      const int at = max8(mine);
-      if (back) {
-        if (at >= 0 || w == 0) {
-          start = max(at, 0);
-          back = false;
-        } else {
-          --w;
-        }
-      }
-    }
-    bool fwd = active;
-    while (__ballot(fwd)) {
-      const uint32_t word[4] = {x.x, x.y, x.z, x.w};
-      int next = 0x7FFFFFFF;
-      const int pos0 = w * 64 + gl * 8;
-#pragma unroll
-      for (int i = 7; i >= 0; --i)
-        if (((word[i >> 1] >> (16 * (i & 1))) & kCandFirst) && pos0 + i > start) next = pos0 + i;
-      const int end = min8(next);
-      if (fwd) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const uint32_t e = (word[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
-          const int pos = pos0 + i;
-          if (pos >= start && pos < end) {
-            if ((e & kCandDead) != kCandDead) atomicAdd(&dec[e & kCandDead], 1u);
-            part[pos] = (uint16_t)(e | kCandDead);
-          }
-        }
-        ++w;
-        fwd = end == 0x7FFFFFFF && w < nwin;
-        if (fwd) x = vec[w * 8 + gl];
-      }
-    }
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(p, d, 64), z = __shfl_down(q, d, 64);
+    if (d <= back) p |= y;
+    if (d <= ahead) q |= z;
   }
+  *to_end = p;
+  *on = q;
 }
 
-// Step j.  Counts before it are base[j mod 2] less what step j-1 took out,
-// dec[(j-1) mod 3]; nothing written here is read by another block of the step.
-// What bounds it: the launch (about 2 us) and a chain of loads (the
-// candidates' counts, the stream, the matched sets), not the stream's bytes:
-// the part's first vectors are loaded before the argmax.
-__global__ __launch_bounds__(kCandStepThreads) void cand_step_kernel(CandArrays c, int most, int j,
+__device__ __forceinline__ unsigned long long max64(unsigned long long x, unsigned long long y) { return x > y ? x : y; }
+
+// The maximum over each row of 16 lanes, in every lane.
+__device__ __forceinline__ unsigned long long row_max64(unsigned long long x) {
+  x = max64(x, dpp64<kDppRowRor + 8>(x));
+  x = max64(x, dpp64<kDppRowRor + 4>(x));
+  x = max64(x, dpp64<kDppRowRor + 2>(x));
+  return max64(x, dpp64<kDppRowRor + 1>(x));
+}
+
+__device__ __forceinline__ unsigned long long lane64(unsigned long long x, int lane) {
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane);
+  return ((unsigned long long)hi << 32) | lo;
+}
+
+// A barrier that orders LDS only, so that loads from global memory stay in flight over it.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Launch j.  Counts before it are base[j mod 2] less what launch j-1 took out,
+// dec[(j-1) mod 3]; nothing written here is read by another block of the launch.
+// What bounds it is a chain of latencies, not the stream's bytes: the launch, the
+// loads (the part's vectors are loaded with the counts), the decision, the scans,
+// the counts' atomics: 10 to 17 us with a decision of 0.9 to 2.4, where one
+// choice per launch took 7 to 8.  Tops in descending order of their keys come from
+// ranks that eight lanes each count while wavefront 0 decides; reducing them and
+// the tops' counts lane by lane instead took 3 to 16 us per launch.
+// The sets' classes come from scans over the stream, which cost the same for any
+// mix of sets.  A walk from every match to both ends of its set took 20 to 190 us
+// in the first launches, where most sets match (LT with in-weights, k = 10 on the
+// 1M-node graph: 188 against 40 us).
+__global__ __launch_bounds__(kCandStepThreads) void cand_step_kernel(CandArrays c, int most, int j, int k,
                                                                       unsigned long long* best) {
-  constexpr int NW = kCandStepThreads / 64;
+  constexpr int NW = kCandStepThreads / 64, ROWS = kCandStepThreads / 16, KEYS = ROWS + kCandTop;
+  constexpr int ORDER = 2 * kCandTop;  // the next tops are the first of these not chosen
+  static_assert(ROWS == 64 && kCandTop == 8 && KEYS % 8 == 0 && kCandStepThreads >= 64 + 8 * KEYS,
+                "a wavefront decides over the rows, eight lanes rank each key");
+  constexpr int VECS = kCandTileVecs, TILE = VECS * kCandStepThreads;  // vectors per thread and tile
+  static_assert(VECS * NW == 64, "a wavefront scans the chunks of a tile");
   __shared__ __align__(16) uint32_t s_dec[kCandMax];
-  __shared__ uint32_t s_hits[NW][kCandHits];
-  __shared__ unsigned long long s_key[NW];
-  __shared__ uint32_t s_num[NW], s_any;
+  __shared__ __align__(16) uint16_t s_cls[kCandMax];
+  __shared__ uint32_t s_chunk[64];  // of a tile's chunks of 64 vectors: head | tail << 12 | kCandStarts
+  __shared__ unsigned long long s_key[KEYS];  // best outside the tops per row of lanes, then the tops
+  __shared__ uint32_t s_num[KEYS];            // their numbers
+  __shared__ __align__(16) uint32_t s_within[kCandCombos];  // sets whose combination is within this one
+  __shared__ uint32_t s_combos[kCandCombos];
+  __shared__ uint32_t s_chosen[kCandTop], s_order[ORDER];
+  __shared__ int s_nchosen;
+  __shared__ uint32_t s_any;
+  __shared__ int s_open[2];
   const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
+  CandHead* head = c.head;
+  const uint32_t t = head->t, picked = head->picked[j & 1];
+  const bool failed = head->failed != 0u;
+  const int nvec = (int)(c.seg_len[blockIdx.x] / 8u);
+  uint16_t* part = c.stream + c.seg_start[blockIdx.x];
+  uint4* vec = reinterpret_cast<uint4*>(part);
   const uint4* base = reinterpret_cast<const uint4*>(c.base + (size_t)(j & 1) * kCandMax);
   uint4* base_next = reinterpret_cast<uint4*>(c.base + (size_t)((j + 1) & 1) * kCandMax);
   const uint4* dec_prev = reinterpret_cast<const uint4*>(c.dec + (size_t)((j + 2) % 3) * kCandMax);
   uint32_t* dec_now = c.dec + (size_t)(j % 3) * kCandMax;
   uint4* dec_next = reinterpret_cast<uint4*>(c.dec + (size_t)((j + 1) % 3) * kCandMax);
   const uint4* node = reinterpret_cast<const uint4*>(c.node);
-  const uint32_t t = c.head->t;
-  const bool failed = c.head->failed != 0u;
-  const int nvec = (int)(c.seg_len[blockIdx.x] / 8u);
-  uint16_t* part = c.stream + c.seg_start[blockIdx.x];
-  const uint4* vec = reinterpret_cast<const uint4*>(part);
-  // the candidate of the largest count, ties to the lowest node: count << 32 | ~node, and its number
+  uint32_t old[kCandTop];
+#pragma unroll
+  for (int i = 0; i < kCandTop; ++i) old[i] = head->tops[j & 1][i];
   constexpr int R = kCandMax / (4 * kCandStepThreads);  // fours of candidates per thread
-  uint4 now[R], id[R];
-  unsigned long long key = 0;
-  uint32_t num = 0;
+  uint4 now[R], taken[R], id[R], x[VECS], row_of[kCandRows];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const int i = r * kCandStepThreads + tid;
     now[r] = make_uint4(kCandTaken, kCandTaken, kCandTaken, kCandTaken);
-    id[r] = make_uint4(0u, 0u, 0u, 0u);
+    taken[r] = id[r] = make_uint4(0u, 0u, 0u, 0u);
     if (4 * i < most) {
-      const uint4 b = base[i], d = dec_prev[i];
+      now[r] = base[i];
+      taken[r] = dec_prev[i];
       id[r] = node[i];
-      now[r] = make_uint4(b.x == kCandTaken ? kCandTaken : b.x - d.x, b.y == kCandTaken ? kCandTaken : b.y - d.y,
-                          b.z == kCandTaken ? kCandTaken : b.z - d.z, b.w == kCandTaken ? kCandTaken : b.w - d.w);
-      reinterpret_cast<uint4*>(s_dec)[i] = make_uint4(0u, 0u, 0u, 0u);
     }
   }
-  uint4 x = make_uint4(~0u, ~0u, ~0u, ~0u);
-  if (tid < nvec) x = vec[tid];
+  if (wv == 0) {
+#pragma unroll
+    for (int i = 0; i < kCandRows; ++i)
+      row_of[i] = reinterpret_cast<const uint4*>(head->combos[(j + 2) % 3][i])[lane];
+  }
+  if (picked >= (uint32_t)k || failed) {  // the same in every block
+    if (blockIdx.x == 0 && tid == 0) head->picked[(j + 1) & 1] = picked;
+    return;
+  }
+#pragma unroll
+  for (int v = 0; v < VECS; ++v) {
+    x[v] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    if (v * kCandStepThreads + tid < nvec) x[v] = vec[v * kCandStepThreads + tid];
+  }
+  if (tid < kCandCombos) s_combos[tid] = 0u;
+  if (tid < kCandTop) s_key[ROWS + tid] = 0ull;
+  if (tid < ORDER) s_order[tid] = 0u;
+  if (tid == 0) {
+    s_any = 0u;
+    s_open[0] = -1;
+  }
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    const uint32_t cv[4] = {now[r].x, now[r].y, now[r].z, now[r].w}, uv[4] = {id[r].x, id[r].y, id[r].z, id[r].w};
+    const int i = r * kCandStepThreads + tid;
+    if (4 * i < most) {
+      reinterpret_cast<uint4*>(s_dec)[i] = make_uint4(0u, 0u, 0u, 0u);
+      reinterpret_cast<uint2*>(s_cls)[i] = make_uint2(0u, 0u);
+    }
+  }
+  uint32_t mine = 0;  // which of this thread's candidates are tops
+#pragma unroll
+  for (int i = 0; i < kCandTop; ++i) {
+    const uint32_t f = old[i] - 1u;
+    if (old[i] && (f / 4u) % (uint32_t)kCandStepThreads == (uint32_t)tid)
+      mine |= 1u << (f / (4u * kCandStepThreads) * 4u + f % 4u);
+  }
+  lds_barrier();
+  // key of a candidate: count << 32 | ~node, so the largest count, ties to the lowest node
+  unsigned long long key = 0;
+  uint32_t num = 0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    uint32_t* cv[4] = {&now[r].x, &now[r].y, &now[r].z, &now[r].w};
+    const uint32_t dv[4] = {taken[r].x, taken[r].y, taken[r].z, taken[r].w};
+    const uint32_t uv[4] = {id[r].x, id[r].y, id[r].z, id[r].w};
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-      const unsigned long long k = ((unsigned long long)cv[w] << 32) | (0xFFFFFFFFull - uv[w]);
-      if (cv[w] != kCandTaken && k > key) {
-        key = k;
-        num = (uint32_t)(4 * (r * kCandStepThreads + tid) + w);
+      if (*cv[w] == kCandTaken) continue;
+      *cv[w] -= dv[w];
+      const unsigned long long q = ((unsigned long long)*cv[w] << 32) | (0xFFFFFFFFull - uv[w]);
+      const uint32_t me = (uint32_t)(4 * (r * kCandStepThreads + tid) + w);
+      if (mine >> (4 * r + w) & 1u) {
+#pragma unroll
+        for (int i = 0; i < kCandTop; ++i)
+          if (old[i] == me + 1u) {
+            s_key[ROWS + i] = q;
+            s_num[ROWS + i] = me;
+          }
+      } else if (q > key) {
+        key = q;
+        num = me;
       }
     }
   }
-  unsigned long long top = key;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long y = __shfl_xor(top, o, 64);
-    top = y > top ? y : top;
-  }
-  // keys differ between candidates: one lane holds the wavefront's top one
-  if (key == top && (top || lane == 0)) {
-    s_key[wv] = top;
-    s_num[wv] = num;
-  }
-  if (tid == 0) s_any = 0u;
-  __syncthreads();
-  top = 0;
-  uint32_t v = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    if (s_key[w] > top) {
-      top = s_key[w];
-      v = s_num[w];
+  {
+    const unsigned long long row = row_max64(key);
+    // keys differ between candidates: one lane of the row holds its best
+    if (key == row && (row || tid % 16 == 0)) {
+      s_key[tid / 16] = row;
+      s_num[tid / 16] = num;
     }
   }
-  const bool ok = !failed && top != 0ull && (uint32_t)(top >> 32) >= t;
+  if (wv == 0) {
+    // sets by combination (lane l: 4l .. 4l + 3), then summed over the combinations within each
+    uint32_t h[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < kCandRows; ++i) {
+      h[0] += row_of[i].x;
+      h[1] += row_of[i].y;
+      h[2] += row_of[i].z;
+      h[3] += row_of[i].w;
+    }
+    h[1] += h[0];
+    h[3] += h[2];
+    h[2] += h[0];
+    h[3] += h[1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t y = dpp32<kDppRowShr + 1>(h[i]);
+      h[i] += lane & 1 ? y : 0u;
+      y = dpp32<kDppRowShr + 2>(h[i]);
+      h[i] += lane & 2 ? y : 0u;
+      y = dpp32<kDppRowShr + 4>(h[i]);
+      h[i] += lane & 4 ? y : 0u;
+      y = dpp32<kDppRowShr + 8>(h[i]);
+      h[i] += lane & 8 ? y : 0u;
+      y = __shfl_xor(h[i], 16, 64);
+      h[i] += lane & 16 ? y : 0u;
+      y = __shfl_xor(h[i], 32, 64);
+      h[i] += lane & 32 ? y : 0u;
+    }
+    reinterpret_cast<uint4*>(s_within)[lane] = make_uint4(h[0], h[1], h[2], h[3]);
+  }
+  lds_barrier();
+  if (wv == 0) {
+    const unsigned long long rows = row_max64(s_key[lane]);
+    const unsigned long long bound =
+        max64(max64(lane64(rows, 0), lane64(rows, 16)), max64(lane64(rows, 32), lane64(rows, 48)));
+    unsigned long long in = lane < kCandTop ? s_key[ROWS + lane] : 0ull;  // lane i: top i
+    unsigned long long top = lane64(row_max64(in), 0);
+    int n = 0;
+    if (bound >= top) {
+      if (bound != 0ull && (uint32_t)(bound >> 32) >= t) {
+        if (s_key[lane] == bound) s_chosen[0] = s_num[lane];
+        if (lane == 0 && blockIdx.x == 0) best[picked] = bound;
+        n = 1;
+      }
+    } else {
+      const uint32_t low = (uint32_t)in;
+      uint32_t left = kCandCombos - 1;      // the tops not chosen
+      bool is_left = in != 0ull;
+      while (top > bound && (uint32_t)(top >> 32) >= t && picked + (uint32_t)n < (uint32_t)k) {
+        const uint64_t who = __ballot(in == top && is_left);
+        const int i = __ffsll((unsigned long long)who) - 1;
+        if (lane == i) {
+          s_chosen[n] = s_num[ROWS + i];
+          is_left = false;
+        }
+        if (lane == 0 && blockIdx.x == 0) best[picked + (uint32_t)n] = top;
+        ++n;
+        left &= ~(1u << i);
+        // a top's sets left: those with none chosen, less those without this top too
+        const uint32_t cnt = s_within[left] - s_within[left & ~(1u << (lane % kCandTop))];
+        in = is_left ? ((unsigned long long)cnt << 32) | low : 0ull;
+        top = lane64(row_max64(in), 0);
+      }
+    }
+    if (lane == 0) s_nchosen = n;
+  } else if (tid < 64 + 8 * KEYS) {
+    // the order of the largest keys
+    const int q = (tid - 64) / 8;
+    const unsigned long long me = s_key[q];
+    uint32_t larger = 0;
+#pragma unroll
+    for (int e = 0; e < KEYS / 8; ++e) larger += s_key[e * 8 + tid % 8] > me ? 1u : 0u;
+    larger = sum8(larger);
+    if (me != 0ull && larger < (uint32_t)ORDER && tid % 8 == 0) s_order[larger] = s_num[q] + 1u;
+  }
+  lds_barrier();
+  const int n = s_nchosen;
+  if (tid < 64) {
+    const uint32_t o = tid < ORDER ? s_order[tid] : 0u;
+    bool next = o != 0u;
+    for (int q = 0; q < n; ++q) next = next && s_chosen[q] != o - 1u;
+    const uint64_t all = __ballot(next);
+    const int at = (int)__popcll(all & ((1ull << lane) - 1ull));
+    if (next && at < kCandTop) s_cls[o - 1u] = (uint16_t)(1u << at);
+    if (blockIdx.x == 0) {
+      if (next && at < kCandTop) head->tops[(j + 1) & 1][at] = o;
+      if (tid < kCandTop && tid >= (int)__popcll(all)) head->tops[(j + 1) & 1][tid] = 0u;
+    }
+  } else if (tid - 64 < n) {
+    s_cls[s_chosen[tid - 64]] = (uint16_t)kCandChosen;
+  }
   if (blockIdx.x == 0) {
     if (tid == 0) {
-      best[j] = ok ? top : 0ull;
-      if (!ok) c.head->failed = 1u;
+      if (n == 0) {
+        best[picked] = 1ull;
+        head->failed = 1u;
+      }
+      head->picked[(j + 1) & 1] = picked + (uint32_t)n;
     }
+    for (int i = tid; i < kCandRows * kCandCombos; i += kCandStepThreads) head->combos[(j + 1) % 3][0][i] = 0u;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       const int i = r * kCandStepThreads + tid;
       if (4 * i < most) {
         uint4 b = now[r];
-        if (v == 4u * (uint32_t)i) b.x = kCandTaken;
-        if (v == 4u * (uint32_t)i + 1u) b.y = kCandTaken;
-        if (v == 4u * (uint32_t)i + 2u) b.z = kCandTaken;
-        if (v == 4u * (uint32_t)i + 3u) b.w = kCandTaken;
+        for (int q = 0; q < n; ++q) {
+          const uint32_t v = s_chosen[q];
+          if (v == 4u * (uint32_t)i) b.x = kCandTaken;
+          if (v == 4u * (uint32_t)i + 1u) b.y = kCandTaken;
+          if (v == 4u * (uint32_t)i + 2u) b.z = kCandTaken;
+          if (v == 4u * (uint32_t)i + 3u) b.w = kCandTaken;
+        }
         base_next[i] = b;
         dec_next[i] = make_uint4(0u, 0u, 0u, 0u);
       }
     }
   }
-  if (!ok) return;
-  int nh = 0;
-  const uint32_t vv = v | (v << 16);
-  for (int i0 = wv * 64; i0 < nvec; i0 += kCandStepThreads) {
-    const int i = i0 + lane;
-    if (i0 >= kCandStepThreads) {
-      x = make_uint4(~0u, ~0u, ~0u, ~0u);
-      if (i < nvec) x = vec[i];
-    }
-    const uint32_t word[4] = {x.x, x.y, x.z, x.w};
-    uint32_t m = 0;
+  if (n == 0 || picked + (uint32_t)n >= (uint32_t)k) return;  // the last choice changes no later step
+  lds_barrier();
+  // of the set open at the tile's start, where there are several tiles: its classes and first entry
+  uint32_t open = 0;
+  int open_at = 0, turn = 0;
+  for (int t0 = 0; t0 < nvec; t0 += TILE) {
+    const bool ends = t0 + TILE >= nvec;
+    uint32_t p[VECS], q[VECS], hits = 0;  // hits: which of the wavefront's chunks have classes
+    uint4 y[VECS];
+    if (!ends) {  // the next tile
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const uint32_t y = (word[w] ^ vv) & 0x7FFF7FFFu;
-      m |= (y & 0xFFFFu) == 0u ? 1u << (2 * w) : 0u;
-      m |= (y >> 16) == 0u ? 2u << (2 * w) : 0u;
-    }
-    uint64_t any = __ballot(m != 0u);
-    while (any) {
-      if (m) {
-        const int bit = __ffs((int)m) - 1;
-        s_hits[wv][nh + (int)__popcll(any & ((1ull << lane) - 1ull))] = (uint32_t)(i * 8 + bit);
-        m &= m - 1u;
+      for (int v = 0; v < VECS; ++v) {
+        const int i = t0 + TILE + v * kCandStepThreads + tid;
+        y[v] = i < nvec ? vec[i] : make_uint4(~0u, ~0u, ~0u, ~0u);
       }
-      nh += (int)__popcll(any);
-      any = __ballot(m != 0u);
     }
-    if (nh > kCandHits - 512) {  // the next 64 vectors may match in 512 entries
-      __builtin_amdgcn_wave_barrier();
-      cand_take_out(part, nvec / 8, s_hits[wv], nh, s_dec, lane);
-      nh = 0;
+#pragma unroll
+    for (int v = 0; v < VECS; ++v) {
+      const uint32_t word[4] = {x[v].x, x[v].y, x[v].z, x[v].w};
+      uint32_t some = 0;
+      p[v] = q[v] = 0u;
+      if (t0 + v * kCandStepThreads + wv * 64 < nvec) {
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+          const uint32_t e = (word[w >> 1] >> (16 * (w & 1))) & kCandDead;
+          if (e != kCandDead) some |= s_cls[e];
+        }
+      }
+      const bool starts = ((word[0] | word[1] | word[2] | word[3]) & 0x80008000u) != 0u;
+      uint32_t sum = __ballot(starts) ? kCandStarts : 0u;
+      if (__ballot(some != 0u)) {
+        hits |= 1u << v;
+        uint32_t head = 0, acc = 0;
+        bool first = true;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+          const uint32_t e = (word[w >> 1] >> (16 * (w & 1))) & 0xFFFFu;
+          if (e & kCandFirst) {
+            if (first) head = acc;
+            first = false;
+            acc = 0;
+          }
+          if ((e & kCandDead) != kCandDead) acc |= s_cls[e & kCandDead];
+        }
+        if (first) head = acc;
+        scan_classes(head, acc, starts, lane, &p[v], &q[v]);
+        sum |= (uint32_t)__builtin_amdgcn_readlane((int)q[v], 0) |
+               (uint32_t)__builtin_amdgcn_readlane((int)p[v], 63) << 12;
+      }
+      if (lane == 0) s_chunk[v * NW + wv] = sum;
+    }
+    lds_barrier();
+    const uint32_t sum = s_chunk[lane];
+    uint32_t cp, cq;
+    scan_classes(sum & 0xFFFu, (sum >> 12) & 0xFFFu, (sum & kCandStarts) != 0u, lane, &cp, &cq);
+    const uint64_t cstarts = __ballot((sum & kCandStarts) != 0u);
+    // the set from before the tile reaches into it, the last one perhaps out of it
+    const bool in_first = !(cstarts & (~0ull >> (63 - lane)));  // no start up to this chunk's end
+    const bool to_last = !(cstarts & (~0ull << lane));          // no start from this chunk on
+    if (in_first) cp |= open;
+    if (to_last && !ends) cq |= kCandOpen;
+#pragma unroll
+    for (int v = 0; v < VECS; ++v) {
+      const int ch = v * NW + wv;
+      const uint32_t in = ch ? (uint32_t)__builtin_amdgcn_readlane((int)cp, ch ? ch - 1 : 0) : open;
+      const uint32_t out = ch < 63 ? (uint32_t)__builtin_amdgcn_readlane((int)cq, ch < 63 ? ch + 1 : 63)
+                                   : (ends ? 0u : kCandOpen);
+      const bool hit = (hits >> v & 1u) != 0u;
+      if (!hit && !(in & kCandChosen) && !(out & ~kCandOpen)) continue;
+      const uint32_t word[4] = {x[v].x, x[v].y, x[v].z, x[v].w};
+      const bool starts = ((word[0] | word[1] | word[2] | word[3]) & 0x80008000u) != 0u;
+      const uint64_t all = __ballot(starts);
+      uint32_t before = __shfl_up(p[v], 1, 64), after = __shfl_down(q[v], 1, 64);  // of the sets open at the lane's ends
+      if (lane == 0) before = 0u;
+      if (lane == 63) after = 0u;
+      if (!(all & ((1ull << lane) - 1ull))) before |= in;
+      if (lane == 63 || !(all & (~0ull << (lane + 1)))) after |= out;
+      uint32_t kill = 0, acc = 0, seg = 0;
+      bool last = true;
+#pragma unroll
+      for (int w = 7; w >= 0; --w) {
+        const uint32_t e = (word[w >> 1] >> (16 * (w & 1))) & 0xFFFFu;
+        if ((e & kCandDead) != kCandDead) {
+          acc |= s_cls[e & kCandDead];
+          seg |= 1u << w;
+        }
+        if (e & kCandFirst) {
+          if (last) acc |= after;
+          last = false;
+          if (!(acc & kCandOpen)) {
+            if (acc & kCandChosen) kill |= seg;
+            else if (acc) atomicAdd(&s_combos[acc], 1u);
+          }
+          acc = seg = 0;
+        }
+      }
+      acc |= before;
+      if (last) acc |= after;
+      if ((acc & kCandChosen) && !(acc & kCandOpen)) kill |= seg;
+      s_any = 1u;
+      if (__ballot(kill != 0u)) {
+        uint32_t dead[4] = {x[v].x, x[v].y, x[v].z, x[v].w};
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+          if (kill >> w & 1u) {
+            atomicAdd(&s_dec[(word[w >> 1] >> (16 * (w & 1))) & kCandDead], 1u);
+            dead[w >> 1] |= kCandDead << (16 * (w & 1));
+          }
+        }
+        if (kill) vec[t0 + v * kCandStepThreads + tid] = make_uint4(dead[0], dead[1], dead[2], dead[3]);
+      }
+    }
+    if (ends && t0 == 0) break;
+    // several tiles: the set that was open before this one, where it ends here, and the one open after it
+    const uint32_t total = open | (uint32_t)__builtin_amdgcn_readlane((int)cq, 0);
+    if (t0 && total && !(total & kCandOpen)) {
+      if (total & kCandChosen) {
+        __syncthreads();  // the stores of earlier tiles are done
+        for (int i = open_at + tid; i < t0 * 8; i += kCandStepThreads) {
+          const uint32_t e = part[i];
+          if ((e & kCandDead) != kCandDead) {
+            atomicAdd(&s_dec[e & kCandDead], 1u);
+            part[i] = (uint16_t)(e | kCandDead);
+          }
+        }
+      } else if (tid == 0) {
+        atomicAdd(&s_combos[total], 1u);
+      }
       s_any = 1u;
     }
-  }
-  if (nh) {
-    __builtin_amdgcn_wave_barrier();
-    cand_take_out(part, nvec / 8, s_hits[wv], nh, s_dec, lane);
-    s_any = 1u;
+    if (ends) break;
+    bool found = false;
+#pragma unroll
+    for (int v = VECS - 1; v >= 0; --v) {
+      const uint32_t word[4] = {x[v].x, x[v].y, x[v].z, x[v].w};
+      int w_last = -1;
+#pragma unroll
+      for (int w = 0; w < 8; ++w)
+        if ((word[w >> 1] >> (16 * (w & 1))) & kCandFirst) w_last = w;
+      const uint64_t all = __ballot(w_last >= 0);
+      if (all && !found && lane == 63 - __clzll((long long)all))
+        atomicMax(&s_open[turn], (t0 + v * kCandStepThreads + tid) * 8 + w_last);
+      found = found || all;
+    }
+    if (tid == 0) s_open[turn ^ 1] = -1;
+    lds_barrier();
+    open = (uint32_t)__builtin_amdgcn_readlane((int)cp, 63);
+    if (s_open[turn] >= 0) open_at = s_open[turn];
+    turn ^= 1;
+#pragma unroll
+    for (int v = 0; v < VECS; ++v) x[v] = y[v];
   }
   __syncthreads();
   if (!s_any) return;
   for (int i = tid; i < most; i += kCandStepThreads)
     if (s_dec[i]) atomicAdd(&dec_now[i], s_dec[i]);
+  if (tid < kCandCombos && s_combos[tid])
+    atomicAdd(&head->combos[j % 3][blockIdx.x % kCandRows][tid], s_combos[tid]);
 }
 
 unsigned grid_for(uint64_t items, unsigned cap) {
@@ -1314,7 +1592,7 @@ CandLayout cand_layout(int64_t n, uint64_t total) {
   CandLayout L;
   size_t at = 0;
   L.head = at;
-  at += 256;
+  at += align256(sizeof(CandHead));
   L.bins = at;
   at += (size_t)kCandBins * 4;
   L.dec = at;
@@ -1363,7 +1641,7 @@ int cand_most(const GreedyArgs& a) { return std::min(kCandMax, std::max(kCandMin
 template <class V>
 void cand_prepare(const GreedyArgs& a, V sets, hipStream_t s) {
   const CandArrays c = cand_arrays(a);
-  hipLaunchKernelGGL(cand_init_kernel, dim3(16), dim3(kThreads), 0, s, c);
+  hipLaunchKernelGGL(cand_init_kernel, dim3(16), dim3(kThreads), 0, s, c, a.best, a.k);
   const unsigned grid = grid_for((uint64_t)a.n, 256);
   const int most = cand_most(a);
   if (a.n > most) hipLaunchKernelGGL(cand_bins_kernel, dim3(grid), dim3(kThreads), 0, s, a.cnt, a.n, c.bins);
@@ -1569,9 +1847,9 @@ void launch_set_u64(unsigned long long* p, unsigned long long v, hipStream_t s) 
 void launch_greedy(const GreedyArgs& a, int k, hipStream_t s) {
   if (use_candidates(a)) {
     const CandArrays c = cand_arrays(a);
-    for (int j = 0; j < k; ++j)
-      hipLaunchKernelGGL(cand_step_kernel, dim3((unsigned)c.segs), dim3(kCandStepThreads), 0, s, c,
-                         cand_most(a), j, a.best);
+    for (int j = a.launched; j < a.launched + cand_launches(k); ++j)
+      hipLaunchKernelGGL(cand_step_kernel, dim3((unsigned)c.segs), dim3(kCandStepThreads), 0, s, c, cand_most(a), j, k,
+                         a.best);
     return;
   }
   launch_greedy_init(a, a.nsets, k, s);

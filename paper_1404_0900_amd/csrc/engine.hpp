@@ -245,8 +245,13 @@ struct GreedyArgs {
   void* bkt;           // optional: bucket_workspace_bytes(n, total, index) for the counting sort by node range
                        // and the candidate greedy
   int k;               // greedy steps of the whole run, or 0 where they are launched one by one
-  int all_nodes;       // nonzero: no candidate greedy (it left a key 0 on this collection)
+  int all_nodes;       // nonzero: no candidate greedy (it left key 1 on this collection)
+  int launched;        // launches of the candidate greedy before this call of launch_greedy
 };
+// Launches of the candidate greedy per call of launch_greedy.  Each takes one or
+// more of its k steps: 4 to 7 launches took k = 10, 6 to 10 k = 25, 13 to 16 k = 50.
+// One that finds all taken costs 4 us, a second call with its readback about 30 us.
+constexpr int cand_launches(int k) { return k / 4 + 5 < k ? k / 4 + 5 : k; }
 // Workspace of the counting sort by node range that launch_counts and
 // launch_index use when GreedyArgs.bkt is set, and (index) of the candidate
 // greedy; 0 where they do not apply.
@@ -254,9 +259,10 @@ size_t bucket_workspace_bytes(int64_t n, uint64_t total, bool index);
 // Coverage counts only (the greedy of k = 1 needs no index).
 void launch_counts(const GreedyArgs& a, hipStream_t s);
 // With bkt and k set, launch_index and launch_greedy run the greedy over the
-// candidates of the largest counts where it applies; a step those do not
-// decide leaves key 0 (no valid key is 0), as do the steps after it, and both
-// are launched again with all_nodes set.
+// candidates of the largest counts where it applies.  launch_greedy then makes
+// cand_launches(k) launches, and while key k-1 is 0 (no choice's key is) it is
+// called again with `launched` advanced by as many.  Key 1 marks a step that the
+// candidates do not decide: both are launched again with all_nodes set.
 void launch_index(const GreedyArgs& a, hipStream_t s);
 void launch_greedy(const GreedyArgs& a, int k, hipStream_t s);
 // The same greedy one step at a time, for collections of which only sets

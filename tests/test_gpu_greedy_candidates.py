@@ -79,3 +79,26 @@ def test_overlapping_hubs_fall_below_the_threshold(eng):
     sets = [np.concatenate([[0], r.choice(np.arange(1, 9001), size=1500, replace=False)]) for _ in range(300)]
     sets += [[10000 + int(x)] for x in r.integers(0, 10000, size=400)]
     _check(eng, n, sets, 25, "overlap")
+
+
+@pytest.mark.parametrize("hubs,noise", [(8, 0), (9, 30), (12, 400), (40, 20)])
+def test_hubs_chosen_together(eng, hubs, noise):
+    """Sets of every mix of a few hubs, whose counts one launch follows over several steps, with other nodes' counts
+    in between."""
+    n, count, k = 30000, 20000, 30
+    r = np.random.default_rng(hubs + noise)
+    sets = []
+    for _ in range(count):
+        s = np.concatenate([np.flatnonzero(r.random(hubs) < 0.3), hubs + r.integers(0, noise, 2) if noise else [],
+                            1000 + r.choice(n - 1000, size=int(r.integers(1, 4)), replace=False)]).astype(np.int32)
+        sets.append(np.unique(s))
+    _check(eng, n, sets, k, "hubs")
+
+
+def test_parts_of_several_tiles(eng):
+    """More candidate entries per block than it holds at once, with long sets over the edges of its tiles."""
+    n = 8192
+    r = np.random.default_rng(0)
+    sets = [r.permutation(n)[:int(s)] for s in r.integers(1, 8000, size=2600)]
+    _check(eng, n, sets, 12, "tiles")
+    _check(eng, n, [x[x % 97 == 0] if len(x) < 4000 else x for x in sets] + [[i] for i in range(900)], 40, "tiles, mixed")
