@@ -420,34 +420,112 @@ constexpr uint64_t kDirectCounts = 1ull << 20;
 constexpr int kBucketMax = 8192;             // buckets (LDS counters per tile of sets)
 constexpr uint32_t kBucketChunk = 1u << 14;  // entries per block of the per-bucket passes
 
-// bcnt[b * kLinePad] += entries of the collection in bucket b.
-template <class V>
-__global__ __launch_bounds__(kThreads) void bucket_hist_kernel(V sets, uint64_t nsets, int shift, int nb,
-                                                               uint32_t* bcnt) {
-  constexpr int TS = kHistTileSets;
-  __shared__ int64_t s_start[TS];
-  __shared__ int64_t s_pre[TS + 1];
-  __shared__ uint32_t s_wtot[kThreads / 64];
-  __shared__ uint32_t h[kBucketMax];
-  for (uint64_t s0 = (uint64_t)blockIdx.x * TS; s0 < nsets; s0 += (uint64_t)gridDim.x * TS) {
-    uint32_t len = 0;
+constexpr int kSortThreads = 512;    // sets per tile of the sort at most, one per thread
+constexpr int kSortWindow = 4096;    // entries per window of a tile
+constexpr unsigned kSortBlocks = 1024;
+
+enum SortPass { kSortCount, kSortMove, kSortMoveIds };
+
+// kSortCount: fill[b * kLinePad] += entries of the collection in bucket b.
+// Otherwise moves every entry (and its set id) into its bucket, fill counting
+// those moved.  A block walks over tiles of ts sets in windows of kSortWindow
+// entries.  An entry's set is the number of set starts up to it: a bit per entry
+// and the starts before each 64 of them.  The entry's place in its bucket is what
+// its LDS counter returns, after those of the windows before.  Bounded by LDS and
+// latency between barriers, not by the entries' bytes.  Against tiles of 256 sets
+// with a binary search for every entry's set, twice for a move, the one-step run on
+// the 1M-node graph takes 0.7 ms for the count (1.27 before) and 1.4 ms for the
+// move (2.5).  512 threads of 90 to 120 registers are better than 1024 (25.4 against
+// 25.7 ms for that run), registers cut to 64 for twice the wavefronts worse (27.4).
+template <class V, SortPass PASS>
+__global__ __launch_bounds__(kSortThreads) void bucket_sort_kernel(V sets, uint64_t nsets, int ts, int shift, int nb,
+                                                                   const int64_t* boff, uint32_t* fill, uint32_t* bu,
+                                                                   uint32_t* bs) {
+  constexpr int NW = kSortThreads / 64;
+  constexpr int NC = kSortWindow / 64;  // 64-entry chunks of a window, one per lane of a wavefront
+  constexpr int PW = NC / NW;           // chunks per wavefront
+  static_assert(NC == 64, "a wavefront scans the chunks of a window");
+  __shared__ unsigned long long red[NW];
+  __shared__ unsigned long long s_marks[NC];
+  __shared__ int64_t s_delta[kSortThreads];
+  __shared__ uint32_t s_id[PASS == kSortMoveIds ? kSortThreads : 1];
+  __shared__ uint32_t s_rank[NC], s_seen;
+  __shared__ uint32_t h[kBucketMax];  // the window's entries per bucket, then where they go
+  const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
+  const uint64_t ntiles = (nsets + (uint64_t)ts - 1) / (uint64_t)ts;
+  if (PASS == kSortCount)
+    for (int i = tid; i < nb; i += kSortThreads) h[i] = 0u;
+  for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    const uint64_t s = tile * (uint64_t)ts + (uint64_t)tid;
+    unsigned long long len = 0;
     int64_t start = 0;
-    if (threadIdx.x < TS && s0 + threadIdx.x < nsets) {
-      start = sets.start(s0 + threadIdx.x);
-      len = sets.len(s0 + threadIdx.x);
+    if (tid < ts && s < nsets) {
+      len = sets.len(s);
+      start = sets.start(s);
     }
-    for (int i = threadIdx.x; i < nb; i += kThreads) h[i] = 0u;
-    tile_prefix<TS>(len, start, s_start, s_pre, s_wtot);
-    const int64_t tot = s_pre[TS];
-    for (int64_t e = threadIdx.x; e < tot; e += kThreads) {
-      const int j = tile_set_of(s_pre, TS, e);
-      const uint32_t u = (uint32_t)sets.nodes[s_start[j] + (e - s_pre[j])];
-      atomicAdd(&h[u >> shift], 1u);
+    // entries (low 40 bits) and non-empty sets (above) before this one
+    unsigned long long all;
+    const unsigned long long ex = block_excl_scan<kSortThreads>(len | (len ? 1ull << 40 : 0ull), red, &all);
+    const uint64_t tot = all & ((1ull << 40) - 1ull), e0 = ex & ((1ull << 40) - 1ull);
+    if (len) {
+      s_delta[ex >> 40] = start - (int64_t)e0;
+      if (PASS == kSortMoveIds) s_id[ex >> 40] = (uint32_t)s;
     }
+    uint32_t seen = 0;  // sets that started before the window
+    for (uint64_t w0 = 0; w0 < tot; w0 += kSortWindow) {
+      if (tid < NC) s_marks[tid] = 0ull;
+      if (PASS != kSortCount)
+        for (int i = tid; i < nb; i += kSortThreads) h[i] = 0u;
+      __syncthreads();
+      if (len && e0 >= w0 && e0 - w0 < kSortWindow) atomicOr(&s_marks[(e0 - w0) / 64], 1ull << ((e0 - w0) % 64));
+      __syncthreads();
+      if (wv == 0) {
+        const uint32_t x = (uint32_t)__popcll(s_marks[lane]);
+        uint32_t inc = x;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const uint32_t y = __shfl_up(inc, o, 64);
+          if (lane >= o) inc += y;
+        }
+        s_rank[lane] = seen + inc - x;
+        if (lane == 63) s_seen = seen + inc;
+      }
+      __syncthreads();
+      seen = s_seen;
+      uint32_t u[PW], rk[PW], at[PW];
+#pragma unroll
+      for (int i = 0; i < PW; ++i) {
+        const int ch = i * NW + wv;
+        const uint64_t e = w0 + (uint64_t)(ch * 64 + lane);
+        u[i] = rk[i] = at[i] = 0u;
+        if (e < tot) {
+          rk[i] = s_rank[ch] + (uint32_t)__popcll(s_marks[ch] & (~0ull >> (63 - lane))) - 1u;
+          u[i] = (uint32_t)sets.nodes[s_delta[rk[i]] + (int64_t)e];
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < PW; ++i)
+        if (w0 + (uint64_t)((i * NW + wv) * 64 + lane) < tot) at[i] = atomicAdd(&h[u[i] >> shift], 1u);
+      __syncthreads();
+      if (PASS == kSortCount) continue;
+      for (int i = tid; i < nb; i += kSortThreads)
+        if (h[i]) h[i] = (uint32_t)boff[i] + atomicAdd(&fill[(size_t)i * kLinePad], h[i]);
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < PW; ++i) {
+        if (w0 + (uint64_t)((i * NW + wv) * 64 + lane) < tot) {
+          const uint32_t pos = h[u[i] >> shift] + at[i];
+          bu[pos] = u[i];
+          if (PASS == kSortMoveIds) bs[pos] = s_id[rk[i]];
+        }
+      }
+      __syncthreads();
+    }
+  }
+  if (PASS == kSortCount) {
     __syncthreads();
-    for (int i = threadIdx.x; i < nb; i += kThreads)
-      if (h[i]) atomicAdd(&bcnt[(size_t)i * kLinePad], h[i]);
-    __syncthreads();
+    for (int i = tid; i < nb; i += kSortThreads)
+      if (h[i]) atomicAdd(&fill[(size_t)i * kLinePad], h[i]);
   }
 }
 
@@ -473,46 +551,6 @@ __global__ __launch_bounds__(kThreads) void bucket_chunks_kernel(const int64_t* 
   if (threadIdx.x == 0) cstart[nb] = (uint32_t)carry;
 }
 
-// Moves every entry (and, for the index, its set id) into its bucket.
-template <class V, bool INDEX>
-__global__ __launch_bounds__(kThreads) void bucket_scatter_kernel(V sets, uint64_t nsets, int shift, int nb,
-                                                                  const int64_t* boff, uint32_t* bfill, uint32_t* bu,
-                                                                  uint32_t* bs) {
-  constexpr int TS = kHistTileSets;
-  __shared__ int64_t s_start[TS];
-  __shared__ int64_t s_pre[TS + 1];
-  __shared__ uint32_t s_wtot[kThreads / 64];
-  __shared__ uint32_t h[kBucketMax];  // the tile's entries per bucket, then their next position
-  for (uint64_t s0 = (uint64_t)blockIdx.x * TS; s0 < nsets; s0 += (uint64_t)gridDim.x * TS) {
-    uint32_t len = 0;
-    int64_t start = 0;
-    if (threadIdx.x < TS && s0 + threadIdx.x < nsets) {
-      start = sets.start(s0 + threadIdx.x);
-      len = sets.len(s0 + threadIdx.x);
-    }
-    for (int i = threadIdx.x; i < nb; i += kThreads) h[i] = 0u;
-    tile_prefix<TS>(len, start, s_start, s_pre, s_wtot);
-    const int64_t tot = s_pre[TS];
-    for (int64_t e = threadIdx.x; e < tot; e += kThreads) {
-      const int j = tile_set_of(s_pre, TS, e);
-      const uint32_t u = (uint32_t)sets.nodes[s_start[j] + (e - s_pre[j])];
-      atomicAdd(&h[u >> shift], 1u);
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < nb; i += kThreads)
-      if (h[i]) h[i] = (uint32_t)boff[i] + atomicAdd(&bfill[(size_t)i * kLinePad], h[i]);
-    __syncthreads();
-    for (int64_t e = threadIdx.x; e < tot; e += kThreads) {
-      const int j = tile_set_of(s_pre, TS, e);
-      const uint32_t u = (uint32_t)sets.nodes[s_start[j] + (e - s_pre[j])];
-      const uint32_t pos = atomicAdd(&h[u >> shift], 1u);
-      bu[pos] = u;
-      if (INDEX) bs[pos] = (uint32_t)(s0 + (uint64_t)j);
-    }
-    __syncthreads();
-  }
-}
-
 // The bucket, first entry and end of chunk blockIdx.x; false past the last chunk.
 __device__ __forceinline__ bool chunk_of(const int64_t* boff, const uint32_t* cstart, const uint32_t* cb, int nb,
                                          uint32_t& b, int64_t& e0, int64_t& e1, bool& alone) {
@@ -525,23 +563,38 @@ __device__ __forceinline__ bool chunk_of(const int64_t* boff, const uint32_t* cs
   return true;
 }
 
+constexpr int kCountThreads = 512;
+
 // cnt of the chunk's node range: stored where the chunk is its bucket's only
 // one, else added with one atomic per node present.
-__global__ __launch_bounds__(kThreads) void bucket_count_kernel(const uint32_t* bu, const int64_t* boff,
+// (0.34 ms for the one-step run on the 1M-node graph; with a 4-byte load per entry
+// and 256 threads 0.61.)
+__global__ __launch_bounds__(kCountThreads) void bucket_count_kernel(const uint32_t* bu, const int64_t* boff,
                                                                 const uint32_t* cstart, const uint32_t* cb, int nb,
                                                                 int shift, int64_t n, uint32_t* cnt) {
-  __shared__ uint32_t lc[1 << kBucketShiftMax];
+  __shared__ __align__(16) uint32_t lc[1 << kBucketShiftMax];
   uint32_t b;
   int64_t e0, e1;
   bool alone;
   if (!chunk_of(boff, cstart, cb, nb, b, e0, e1, alone)) return;
   const int range = 1 << shift;
   const uint32_t base = b << shift;
-  for (int i = threadIdx.x; i < range; i += kThreads) lc[i] = 0u;
+  for (int i = threadIdx.x; i < range / 4; i += kCountThreads) reinterpret_cast<uint4*>(lc)[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
-  for (int64_t e = e0 + threadIdx.x; e < e1; e += kThreads) atomicAdd(&lc[bu[e] - base], 1u);
+  // four entries per load between the chunk's 16-byte boundaries
+  const int64_t v0 = min((e0 + 3) & ~(int64_t)3, e1), v1 = max(e1 & ~(int64_t)3, v0);
+  if (e0 + threadIdx.x < v0) atomicAdd(&lc[bu[e0 + threadIdx.x] - base], 1u);
+  if (v1 + threadIdx.x < e1) atomicAdd(&lc[bu[v1 + threadIdx.x] - base], 1u);
+#pragma unroll 4
+  for (int64_t e = v0 + 4 * threadIdx.x; e < v1; e += 4 * kCountThreads) {
+    const uint4 u = *reinterpret_cast<const uint4*>(bu + e);
+    atomicAdd(&lc[u.x - base], 1u);
+    atomicAdd(&lc[u.y - base], 1u);
+    atomicAdd(&lc[u.z - base], 1u);
+    atomicAdd(&lc[u.w - base], 1u);
+  }
   __syncthreads();
-  for (int i = threadIdx.x; i < range && (int64_t)base + i < n; i += kThreads) {
+  for (int i = threadIdx.x; i < range && (int64_t)base + i < n; i += kCountThreads) {
     if (alone) cnt[base + i] = lc[i];
     else if (lc[i]) atomicAdd(&cnt[base + i], lc[i]);
   }
@@ -1566,19 +1619,22 @@ void bucket_counts(const GreedyArgs& a, V sets, const BucketLayout& L, bool inde
   // the padded counts and cursors are adjacent: one clear; the scan reads the counts unpadded
   const uint64_t zlen = (uint64_t)(L.bfill - L.bcnt_s) / 4 + (uint64_t)L.nb * kLinePad;
   hipLaunchKernelGGL(zero_u32, dim3(grid_for(zlen, 64)), dim3(kThreads), 0, s, bcnt_s, zlen);
-  const unsigned grid = tile_grid(a.nsets, kHistTileSets);
-  hipLaunchKernelGGL(bucket_hist_kernel<V>, dim3(grid), dim3(kThreads), 0, s, sets, a.nsets, L.shift, L.nb, bcnt_s);
+  // tiles of as many sets as leave each block one, at most one per thread
+  const int ts = (int)std::min<uint64_t>(kSortThreads, std::max<uint64_t>(64, a.nsets / kSortBlocks + 1));
+  const unsigned grid = (unsigned)std::min<uint64_t>(kSortBlocks, (a.nsets + (uint64_t)ts - 1) / (uint64_t)ts);
+  hipLaunchKernelGGL((bucket_sort_kernel<V, kSortCount>), dim3(grid), dim3(kSortThreads), 0, s, sets, a.nsets, ts,
+                     L.shift, L.nb, nullptr, bcnt_s, nullptr, nullptr);
   hipLaunchKernelGGL(unpad_u32, dim3(grid_for((uint64_t)L.nb, 64)), dim3(kThreads), 0, s, bcnt_s, bcnt, L.nb);
   launch_scan_u32_to_i64(bcnt, boff, (uint64_t)L.nb, at_offset<void>(a.bkt, L.temp), s);
   hipLaunchKernelGGL(bucket_chunks_kernel, dim3(1), dim3(kThreads), 0, s, boff, L.nb, cstart, cb);
   uint32_t* bfill = at_offset<uint32_t>(a.bkt, L.bfill);
   if (index)
-    hipLaunchKernelGGL((bucket_scatter_kernel<V, true>), dim3(grid), dim3(kThreads), 0, s, sets, a.nsets, L.shift,
-                       L.nb, boff, bfill, bu, bs);
+    hipLaunchKernelGGL((bucket_sort_kernel<V, kSortMoveIds>), dim3(grid), dim3(kSortThreads), 0, s, sets, a.nsets, ts,
+                       L.shift, L.nb, boff, bfill, bu, bs);
   else
-    hipLaunchKernelGGL((bucket_scatter_kernel<V, false>), dim3(grid), dim3(kThreads), 0, s, sets, a.nsets, L.shift,
-                       L.nb, boff, bfill, bu, bs);
-  hipLaunchKernelGGL(bucket_count_kernel, dim3((unsigned)L.max_chunks), dim3(kThreads), 0, s, bu, boff, cstart, cb,
+    hipLaunchKernelGGL((bucket_sort_kernel<V, kSortMove>), dim3(grid), dim3(kSortThreads), 0, s, sets, a.nsets, ts,
+                       L.shift, L.nb, boff, bfill, bu, bs);
+  hipLaunchKernelGGL(bucket_count_kernel, dim3((unsigned)L.max_chunks), dim3(kCountThreads), 0, s, bu, boff, cstart, cb,
                      L.nb, L.shift, a.n, a.cnt);
 }
 
