@@ -724,8 +724,9 @@ tim_status greedy(tim_ctx* c, int64_t n, uint64_t nsets, const int64_t* set_off,
       c->prof.index_ms += ms_index;
       c->prof.greedy_ms += ms_greedy;
     }
-    // keys left 0: more launches over the candidates; a key of 1: they do not decide that step, so over all nodes
-    again = keys[(size_t)k - 1] == 0ull && !a.all_nodes;
+    // keys left 0: more launches over the candidates; a key of 1 (the last one too): they do not decide that step, so
+    // over all nodes
+    again = keys[(size_t)k - 1] <= 1ull && !a.all_nodes;
     a.launched += tim::cand_launches(k);
     if (again && (a.launched >= k + tim::cand_launches(k) || std::find(keys.begin(), keys.end(), 1ull) != keys.end())) {
       a.all_nodes = 1;

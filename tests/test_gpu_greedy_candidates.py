@@ -102,3 +102,15 @@ def test_parts_of_several_tiles(eng):
     sets = [r.permutation(n)[:int(s)] for s in r.integers(1, 8000, size=2600)]
     _check(eng, n, sets, 12, "tiles")
     _check(eng, n, [x[x % 97 == 0] if len(x) < 4000 else x for x in sets] + [[i] for i in range(900)], 40, "tiles, mixed")
+
+
+@pytest.mark.parametrize("k", [2, 3, 4, 9])
+def test_the_last_step_falls_below_the_threshold(eng, k):
+    """k - 1 hubs that the candidates decide, the first of which covers all sets of the other candidates: only the last
+    step needs a node outside them."""
+    n = 20000
+    r = np.random.default_rng(k)
+    sets = [np.concatenate([[0], r.choice(np.arange(100, 9100), size=1500, replace=False)]) for _ in range(300)]
+    sets += [[i] for i in range(1, k - 1) for _ in range(250 - 10 * i)]
+    sets += [[10000 + int(x)] for x in r.integers(0, 10000, size=400)]
+    _check(eng, n, sets, k, "last step")
