@@ -43,6 +43,7 @@ expected spread of the seeds by 10^4 forward Monte-Carlo runs (tim_spread_mc).
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -65,11 +66,11 @@ MODES = ("widths", "store", "cover")
 # WRITE_SIZE runs of this benchmark (scaled by a plain-copy calibration; see
 # profiles/ic_seg_kernel_chunglu_n1e6_m1e7.md), for the shapes the autotuner
 # picks on this graph.  Valid only for the kernel sources they were taken on.
-TRAFFIC = {
+TRAFFIC = {  # by shape (kernel_name); both are ic_pool_kernel's
     "ic_seg_kernel<1, true, 8, 128, 0, 512, 1> (store)": {
-        "sources_sha256_16": "f04a4aa503ad565e", "taken": "2026-12-03", "fetch_bytes": 2906637862, "write_bytes": 571520432},
+        "sources_sha256_16": "f6456fde9b9b0942", "taken": "2026-12-05", "fetch_bytes": 2021886916, "write_bytes": 333056997},
     "ic_seg_kernel<0, true, 8, 128, 0, 512, 1> (widths)": {
-        "sources_sha256_16": "f04a4aa503ad565e", "taken": "2026-12-03", "fetch_bytes": 2645093577, "write_bytes": 104174699},
+        "sources_sha256_16": "f6456fde9b9b0942", "taken": "2026-12-05", "fetch_bytes": 2728046249, "write_bytes": 91489653},
 }
 KERNEL_SOURCES = ("paper_1404_0900_amd/csrc/sample.hip", "paper_1404_0900_amd/csrc/rng.hpp",
                   "paper_1404_0900_amd/csrc/pick.hpp", "paper_1404_0900_amd/csrc/engine.hpp")
@@ -77,7 +78,6 @@ KERNEL_SOURCES = ("paper_1404_0900_amd/csrc/sample.hip", "paper_1404_0900_amd/cs
 
 def sources_sha():
     """Hash of the kernel sources' code: comments and blank lines do not count."""
-    import re
     h = hashlib.sha256()
     for p in KERNEL_SOURCES:
         with open(os.path.join(ROOT, p), encoding="utf-8") as f:
@@ -89,8 +89,8 @@ def sources_sha():
 
 
 def kernel_name(model, mode, lanes=None):
-    """Tier-0 sampler kernel of (model, mode) as rocprofv3 lists it (template arguments: mode, WC, lanes per set,
-    queue length, log2 of the hash size, group limit, groups per lane)."""
+    """Tier-0 sampler kernel of (model, mode) by its shape (template arguments: mode, WC, lanes per set, queue length,
+    log2 of the hash size, group limit, groups per lane); listed_kernel gives the name in a trace."""
     if model == 1:
         return f"lt_lane_kernel<{mode}> ({MODES[mode]})"
     if lanes is None:
@@ -100,6 +100,12 @@ def kernel_name(model, mode, lanes=None):
     hlog = {4: 0, 8: 0, 16: 8, 32: 9, 64: 10}[lanes]
     gmax = {4: 256, 8: 512, 16: 512, 32: 1024, 64: 2048}[lanes]
     return f"ic_seg_kernel<{mode}, true, {lanes}, {q}, {hlog}, {gmax}, {SEG_GROUPS}> ({MODES[mode]})"
+
+
+def listed_kernel(name):
+    """The kernel as rocprofv3 lists it: the default 8-lane IC shape is ic_pool_kernel's (mode, WC)."""
+    m = re.match(r"ic_seg_(batch_)?kernel<(\d), (true|false), 8, .*> (\(\w+\))$", name)
+    return f"ic_pool_{m[1] or ''}kernel<{m[2]}, {m[3]}> {m[4]}" if m else name
 
 
 def log(msg):
@@ -208,18 +214,21 @@ def main():
         f"{t['sources_sha256_16']} (profiles/), scaled by a plain-copy calibration"
         if roofline["traffic"] is not None else
         "null: no counter run on the current kernel sources " + sources_sha())
+    roofline["kernel"] = listed_kernel(roofline["kernel"])
     sampler_ms = sum(prof.sampler[a][b].kernel_ms + prof.sampler[a][b].large_ms for a in (0, 1) for b in (0, 1, 2))
     sampler_ms += sum(prof.ic_wide[b].kernel_ms + prof.ic_wide[b].large_ms for b in (0, 1, 2))
     sampler_ms += sum(prof.grouped[a].kernel_ms + prof.grouped[a].large_ms for a in (0, 1))
     by_phase = sampler_by_mode(prof, 0)
     roofline_widths = kernel_roofline(prof, 0, 0, name_of, traffic_of)
+    if roofline_widths:
+        roofline_widths["kernel"] = listed_kernel(roofline_widths["kernel"])
     ig_ms = prof.index_ms + prof.greedy_ms
     ig_bytes = GREEDY_BYTES_PER_ENTRY * greedy_entries + greedy_argmax_bytes
     ig_gbs = ig_bytes / (ig_ms * 1e-3) / 1e9 if ig_ms > 0 else 0.0
     roofline_index_greedy = {
         "bound": "hbm", "achieved": round(ig_gbs, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": round(ig_gbs / HBM_PEAK_GBS, 5), "traffic": None,
-        "kernels": "inverted index (counts, scan, scatter) and greedy (argmax, cover) of every query",
+        "kernels": "counts, candidate stream or inverted index, and greedy steps of every query",
         "entries_per_step": greedy_entries // args.steps, "bytes_per_entry": GREEDY_BYTES_PER_ENTRY,
         "argmax_bytes_per_step": greedy_argmax_bytes // args.steps, "gpu_ms_per_step": round(ig_ms / args.steps, 3)}
 
@@ -425,7 +434,7 @@ def kernel_roofline(prof, model, mode, name_of, traffic_of=lambda model, mode: N
 
 
 def batch_kernel_name(model, mode):
-    """Tier-0 kernel of the batched launches as rocprofv3 lists it."""
+    """Tier-0 kernel of the batched launches by its shape, as kernel_name."""
     if model == 1:
         return f"lt_lane_batch_kernel<{mode}> ({MODES[mode]})"
     return f"ic_seg_batch_kernel<{mode}, false, 8, 128, 0, 512, {SEG_GROUPS}> ({MODES[mode]})"
@@ -520,6 +529,7 @@ def batch_measure(steps, warmup):
     prof = eng.read_profile()
     eng.profile(False)
     roofline = dominant_roofline(prof, batch_kernel_name)
+    roofline["kernel"] = listed_kernel(roofline["kernel"])
 
     slow = sorted(((r.ms_total, q["name"]) for (_, _, r), q in zip(seq, queries)), reverse=True)[:5]
     out = {
