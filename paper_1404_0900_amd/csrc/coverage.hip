@@ -415,7 +415,8 @@ __global__ __launch_bounds__(kThreads) void scatter_kernel(V sets, uint64_t nset
 constexpr int kBucketShiftMin = 13, kBucketShiftMax = 13;
 // Collections of at most kDirectCounts entries are counted by the direct pass:
 // the sort's eight launches cost more than its atomics save (0.7M entries: 2%
-// of the 1.5 ms of a TIM+ run on 15K nodes; at 2 to 4M entries the two are even).
+// of the 1.15 ms of a TIM+ run on 15K nodes; at 1 to 2M entries the sort gains 1% on
+// stored sets of 300K nodes).
 constexpr uint64_t kDirectCounts = 1ull << 20;
 constexpr int kBucketMax = 8192;             // buckets (LDS counters per tile of sets)
 constexpr uint32_t kBucketChunk = 1u << 14;  // entries per block of the per-bucket passes
