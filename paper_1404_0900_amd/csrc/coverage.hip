@@ -313,10 +313,14 @@ __device__ __forceinline__ void tile_apply(const int32_t* nodes, TileShared<TS>&
   __syncthreads();
 }
 
-// cnt[u] += number of sets containing u, over a flat entry array.
-__global__ __launch_bounds__(kThreads) void hist_flat_kernel(const int32_t* nodes, uint64_t total, uint32_t* cnt) {
+// cnt[u] += number of sets containing u, over the entries [set_off[0], total)
+// of a CSR (a caller's offsets may be a slice of a larger collection's, whose
+// first set does not start at entry 0).
+__global__ __launch_bounds__(kThreads) void hist_flat_kernel(const int64_t* set_off, const int32_t* nodes,
+                                                             uint64_t total, uint32_t* cnt) {
   __shared__ uint32_t s_key[kAgg], s_cnt[kAgg];
-  for (uint64_t t0 = (uint64_t)blockIdx.x * kTileEntries; t0 < total; t0 += (uint64_t)gridDim.x * kTileEntries) {
+  for (uint64_t t0 = (uint64_t)set_off[0] + (uint64_t)blockIdx.x * kTileEntries; t0 < total;
+       t0 += (uint64_t)gridDim.x * kTileEntries) {
     agg_clear(s_key, s_cnt);
     __syncthreads();
     const uint64_t t1 = min(t0 + (uint64_t)kTileEntries, total);
@@ -1732,8 +1736,8 @@ void launch_counts(const GreedyArgs& a, hipStream_t s) {
   }
   if (a.set_off) {
     if (a.total)
-      hipLaunchKernelGGL(hist_flat_kernel, dim3(tile_grid(a.total, kTileEntries)), dim3(kThreads), 0, s, a.nodes,
-                         a.total, a.cnt);
+      hipLaunchKernelGGL(hist_flat_kernel, dim3(tile_grid(a.total, kTileEntries)), dim3(kThreads), 0, s, a.set_off,
+                         a.nodes, a.total, a.cnt);
   } else {
     hipLaunchKernelGGL(hist_sets_kernel<PoolSets>, dim3(tile_grid(a.nsets, kHistTileSets)), dim3(kThreads), 0, s,
                        pool_of(a), a.nsets, a.cnt);
