@@ -2242,10 +2242,13 @@ __global__ __launch_bounds__(kWave) void lt_hash_kernel(SampleArgs a, TierIO io)
   lt_chain_run<MODE, true>(a, io, true);
 }
 
-// Takes what lt_hash_kernel has left (nothing, where that kernel ran).
+// The lists that lt_hash_kernel leaves alone.  The list's length, which no
+// block changes, decides: the work cursor moves while blocks start, and
+// wavefronts of one block that disagreed on it would leave the block's
+// accumulators uncleared or its last flush undone.
 template <int MODE>
 __global__ __launch_bounds__(kChainWaves* kWave) void lt_chain_kernel(SampleArgs a, TierIO io) {
-  if (a.ctr[io.next_ctr] >= list_len(a, io.in_len_ctr)) return;
+  if (list_len(a, io.in_len_ctr) <= kLtHashMost) return;
   __shared__ BlockAcc blk;
   block_acc_init(blk);
   lt_chain_run<MODE, false>(a, io, true, &blk);
