@@ -414,10 +414,15 @@ uint64_t emit_waves(const tim_ctx* c, int64_t n, int model, uint64_t count) {
   return std::max(waves, w2);
 }
 
+// Largest set the default IC first tier stores for this context.
+uint32_t pool_set_cap(const tim_ctx* c) { return c->budget ? tim::kPoolSetCapBudget : tim::kPoolSetCap; }
+
 // Largest set tier 0 stores (its LDS queue or chain) in emit launches of
 // `count` sets.
 uint64_t tier0_cap(const tim_ctx* c, int64_t n, int model, uint64_t count) {
-  return tim::tier0_set_cap(model, launch_lanes(c, n, model, tim::kModeEmit, std::min(count, kMaxLaunchSets)));
+  const int lanes = launch_lanes(c, n, model, tim::kModeEmit, std::min(count, kMaxLaunchSets));
+  const uint32_t cap = tim::tier0_set_cap(model, lanes);
+  return model == TIM_MODEL_IC && lanes == 8 ? std::min(cap, pool_set_cap(c)) : cap;
 }
 
 // Node-pool slice for launches of `count` sets holding about `nodes`
@@ -487,6 +492,7 @@ tim_status sample_launch(tim_ctx* c, const tim_graph* g, int model, int mode, ui
     a.pool_cap = pool_base < cap ? cap - pool_base : 0;
     a.pool_base = pool_base;
     a.pool_chunk = c->slice;
+    a.set_cap = pool_set_cap(c);
     a.set_start = c->set_start.as<uint64_t>() + set_offset;
     a.set_len = c->set_len.as<uint32_t>() + set_offset;
   }

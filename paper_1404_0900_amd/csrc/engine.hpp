@@ -64,6 +64,17 @@ struct TierIO {
 // default; SampleArgs::pool_chunk sets it per launch).
 constexpr uint32_t kPoolChunk = 2048;
 
+// Nodes of the largest set that the default IC first tier keeps, and of the
+// largest it stores under a device-memory budget (SampleArgs::set_cap).  The
+// node pool is planned for what a wavefront can leave unused, which grows with
+// that size: with 160 nodes a context with a budget of 600 KB refused a query
+// that 128 nodes leave room for, and larger budgets kept up to a tenth fewer
+// sets resident.  Without a budget the pool is a small part of the memory, and
+// storing sets of up to 160 nodes takes 7% off a k = 1 run on the 1M-node graph
+// (24.1 -> 22.5 ms).
+constexpr uint32_t kPoolSetCap = 160;
+constexpr uint32_t kPoolSetCapBudget = 128;
+
 struct GraphView {
   const int64_t* off;   // n+1
   const uint32_t* off32;  // the same offsets in 32 bits (m < 2^32), for the IC first tiers
@@ -94,6 +105,7 @@ struct SampleArgs {
   uint64_t pool_cap;              // entries in it
   uint64_t pool_base;             // its offset in the whole pool (added to set_start)
   uint32_t pool_chunk;            // entries a wavefront reserves at a time (>= 1)
+  uint32_t set_cap;               // emit: the default IC first tier stores sets of at most this many nodes
   uint64_t* set_start;            // emit: pool offset of each set
   uint32_t* set_len;              // emit: size of each set
   const uint32_t* seed_bits;      // cover: n-bit membership of the seed set

@@ -859,7 +859,7 @@ __global__ __launch_bounds__(kSegThreads) void ic_seg_kernel(SampleArgs a, TierI
 constexpr int kPoolLanes = 4;
 constexpr int kPoolBlock = 32;
 constexpr int kPoolShared = 16;                    // blocks the wavefront's sets share (at most 32)
-constexpr int kPoolQ = 5 * kPoolBlock;             // largest set: its own block and four more
+constexpr int kPoolQ = kPoolSetCap;                // largest set: its own block and four more
 constexpr int kPoolSigLog = 5;                     // signature words per set: 2^5 (1024 bits)
 constexpr uint32_t kPoolGroups = 4096;
 constexpr uint32_t kPoolWide = 32;                 // (16: 28.5 against 27.2 ms)
@@ -894,6 +894,7 @@ __device__ __forceinline__ void ic_pool_run(const SampleArgs& a, const TierIO& i
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
   int32_t* nodes = s_node[wv];
   const GraphView g = a.g;
+  const uint32_t most = MODE == kModeEmit ? min((uint32_t)Q, a.set_cap) : (uint32_t)Q;  // nodes of the largest set kept
   const Key key = make_key(a.seed);
   const unsigned long long total = a.count;
   const uint32_t first_lo = (uint32_t)a.first, first_hi = (uint32_t)(a.first >> 32);
@@ -926,7 +927,7 @@ __device__ __forceinline__ void ic_pool_run(const SampleArgs& a, const TierIO& i
     // ---- A: complete sets are finished (or deferred) once none of their
     // groups waits, kPoolFinish of them at a time while others have work left
     const uint32_t now = has ? s_tail[seg] : 0u;
-    const bool over = now > (uint32_t)Q || gsum > kPoolGroups;
+    const bool over = now > most || gsum > kPoolGroups;
     const bool hit = MODE == kModeCover && has && s_hit[seg] != 0u;
     const bool complete = has && (int)(last_end - cons) <= 0 && (over || hit || head >= (int)now);
     const uint64_t busy = __ballot(has && !complete);
@@ -1040,7 +1041,7 @@ __device__ __forceinline__ void ic_pool_run(const SampleArgs& a, const TierIO& i
     if (has) {
       const uint32_t tail = s_tail[seg];
       const bool hit = MODE == kModeCover && s_hit[seg] != 0u;
-      if (tail <= (uint32_t)Q && gsum <= kPoolGroups && !hit) {
+      if (tail <= most && gsum <= kPoolGroups && !hit) {
         const int nb = min((int)tail - head, SL);
         if (sl < nb) {
           const int32_t v = nodes[place(sw, tab, (uint32_t)(head + sl))];
@@ -1156,7 +1157,7 @@ __device__ __forceinline__ void ic_pool_run(const SampleArgs& a, const TierIO& i
       // appends: by at most Q nodes of one step, so from one to four blocks.
       auto grow = [&]() {
         const uint32_t tail = s_tail[seg];
-        const uint32_t need = has && tail <= (uint32_t)Q ? (tail - 1u) / B : 0u;
+        const uint32_t need = has && tail <= most ? (tail - 1u) / B : 0u;
         uint64_t gm = __ballot(is_leader && need > nblk);
         if (!gm) return;
         while (gm) {
@@ -1184,7 +1185,7 @@ __device__ __forceinline__ void ic_pool_run(const SampleArgs& a, const TierIO& i
       };
       grow();
       if (nfast) {
-        const bool room = s_tail[os] <= (uint32_t)Q;  // else the set is deferred, and may lack blocks
+        const bool room = s_tail[os] <= most;  // else the set is deferred, and may lack blocks
         const uint32_t blocks = s_tab[os];
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
@@ -1207,7 +1208,7 @@ __device__ __forceinline__ void ic_pool_run(const SampleArgs& a, const TierIO& i
         const int32_t u = __builtin_amdgcn_readlane(w == 0 ? sv[0] : w == 1 ? sv[1] : w == 2 ? sv[2] : sv[3], src);
         const int row = __builtin_amdgcn_readlane(orow, src);
         const uint32_t tail = s_tail[wv * NS + row];
-        if (tail > (uint32_t)Q) continue;  // outgrown: deferred whatever this source is
+        if (tail > most) continue;  // outgrown: deferred whatever this source is
         const uint32_t blocks = s_tab[wv * NS + row];
         bool found = false;
         for (uint32_t i = (uint32_t)lane; i < tail; i += kWave) found |= nodes[place(row, blocks, i)] == u;
@@ -1216,7 +1217,7 @@ __device__ __forceinline__ void ic_pool_run(const SampleArgs& a, const TierIO& i
           wave_sync();
           grow();
           if (lane == 0) {
-            if (s_tail[wv * NS + row] <= (uint32_t)Q) nodes[place(row, s_tab[wv * NS + row], tail)] = u;
+            if (s_tail[wv * NS + row] <= most) nodes[place(row, s_tab[wv * NS + row], tail)] = u;
             if (MODE == kModeCover && in_seed(a.seed_bits, u)) s_hit[wv * NS + row] = 1u;
           }
           wave_sync();
