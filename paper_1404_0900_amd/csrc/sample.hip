@@ -2021,12 +2021,16 @@ constexpr int kChainWaves = 4;  // wavefronts per block of the long-chain tier
 // graphs of 100K to 1M nodes; none had more than 120 nodes), so the launch lasts
 // as long as one of them.  A launch of at most kLtHashMost such chains therefore
 // walks them once, marking the nodes in an LDS table per lane, with few chains
-// per wavefront; a chain of kLtHashCap nodes goes on with the search.  With 64 KB
+// per wavefront; a chain of kLtHashCap nodes goes on with the search from there
+// (20000 widths on cycles of 250 nodes: 1.10 ms by the search alone, 1.19 so, 1.33
+// with a search that starts at the root again; on random chains of 690 nodes, 404
+// widths: 9.2 and 6.2 ms).  With 64 KB
 // of tables per wavefront only two fit a CU: longer lists keep to the search,
 // which fills the chip.  LT with in-weights on the 1M-node graph: 753 to 885 us
 // per launch by the search, 160 us with tables (TIM+ with k = 10: 8.2 -> 5.7 ms).
 constexpr int kLtHashLog = 8;
 constexpr uint32_t kLtHashCap = 192;
+constexpr uint32_t kLtHashSave = 128;  // the largest power of two below: the search's tortoise stands at node 127 then
 constexpr int kLtHashBlocks = 512;  // one wavefront each, two per CU
 constexpr unsigned long long kLtHashMost = (unsigned long long)kLtHashBlocks * kWave;
 
@@ -2109,9 +2113,14 @@ __device__ __forceinline__ void lt_chain_run(const SampleArgs& a, const TierIO& 
             acc.covered += 1;
             done = true;
           } else if (len == kLtHashCap) {
+            // these are distinct: the search goes on from where it would be after as many steps
             phase = kSearch;
-            cur = x0;
+            pos = kLtHashCap - 1;
+            power = kLtHashSave;
+            lam = kLtHashCap - kLtHashSave;
             width = 0;
+          } else if (len == kLtHashSave) {
+            tort = nx;
           }
         } else if (MODE != kModeEmit) {
           done = true;
@@ -2207,15 +2216,17 @@ __device__ __forceinline__ void lt_chain_run(const SampleArgs& a, const TierIO& 
         }
       }
     }
-    if (HASH && MODE == kModeEmit) {
-      uint64_t m = __ballot(marked);
-      while (m) {  // the wavefront copies the table's nodes
+    uint64_t m = HASH && MODE == kModeEmit ? __ballot(marked) : 0ull;
+    if (m) {  // room for all the walks that end in this step, then the wavefront copies each table's nodes
+      const uint32_t mine = marked ? len : 0u, upto = seg_incl_scan<kWave>(mine, lane);
+      unsigned long long first = 0;
+      if (lane == kWave - 1) first = atomicAdd(&a.ctr[kCtrPoolCursor], (unsigned long long)upto);
+      first = __shfl(first, kWave - 1);
+      while (m) {
         const int row = __ffsll((unsigned long long)m) - 1;
         m &= m - 1ull;
         const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)len, row);
-        unsigned long long at = 0;
-        if (lane == 0) at = atomicAdd(&a.ctr[kCtrPoolCursor], (unsigned long long)n);
-        at = lane0_u64(at);
+        const unsigned long long at = first + (uint32_t)__builtin_amdgcn_readlane((int)upto, row) - n;
         uint32_t out = 0;
         for (int i = lane; i < SLOTS; i += kWave) {
           const uint32_t k = s_tab[HASH ? row : 0][HASH ? i : 0];
