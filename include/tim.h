@@ -227,8 +227,9 @@ typedef struct {
   tim_kernel_profile sampler[2][3]; /* [model][0: widths, 1: stored sets, 2: coverage] */
   uint64_t index_calls;             /* inverted-index builds + greedy runs */
   double index_ms, greedy_ms;
-  tim_kernel_profile ic_wide[3];    /* IC launches of few sets (fewer than n / 20 and 262144), which run the
-                                       64-lane first tier; sampler[0][] holds the others */
+  tim_kernel_profile ic_wide[3];    /* IC launches of few sets (fewer than n / 20 and 262144; with 8 edges per
+                                       node or more fewer than 65536 at least), which run the 64-lane first
+                                       tier; sampler[0][] holds the others */
   tim_kernel_profile grouped[2];    /* [model] multi-job launches that run several early KptEstimation rounds
                                        at once, one job per round; sets counts every set they sampled,
                                        those of rounds past the stopping one included */

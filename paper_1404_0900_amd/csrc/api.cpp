@@ -367,28 +367,37 @@ void hub_submit(Hub* h, Pending* p) {
 // largest set takes to cross its BFS levels, which one wavefront per set crosses
 // fastest, and sixteen sets per wavefront (the default shape) only pay once the
 // sets fill the chip.  Where that is depends on how wide the sets get, which
-// grows with the graph: width launches of 2000, 8000, 30000 and 100000 sets took
-// 93, 165, 207 us (64 lanes) against 89, 99, 143 us on 15K nodes; 143, 206, 334,
-// 551 against 224, 280, 381, 474 us on 1M nodes; and the two were even at 12000
-// sets on 300K nodes.  So the line is one set per kWideNodes nodes, and at most
-// kWideLaunchSets.  Stored sets take it too, with the node-pool bound of that
-// shape (tier0_cap), except in the chunked collections, which plan their pool
-// for the context's shape.  Batched launches keep theirs.
+// grows with the graph and with its in-lists.
+// Fewer than kWideDegree edges per node: one set per kWideNodes nodes, at most
+// kWideLaunchSets (width launches of 3000, 30000 and 100000 sets on 15K nodes
+// with 4 edges each took 125, 206, 272 us with 64 lanes and 108, 161, 199 with
+// the default; 8000, 60000, 200000 sets on 150K nodes 169, 260, 363 and 97, 185,
+// 214).
+// More edges: at least kWideDense sets (15K nodes with 16 edges each, 3000,
+// 30000, 100000 sets: 177, 244, 407 and 308, 355, 411; with 50 edges, 30000 and
+// 120000 sets: 624, 939 and 768, 940; 1M nodes with 10, 40000, 60000, 200000 sets:
+// 426, 483, 747 and 428, 465, 561).
+// Stored sets take it too, with the node-pool bound of that shape (tier0_cap),
+// except in the chunked collections, which plan their pool for the context's
+// shape.  Batched launches keep theirs.
 constexpr uint64_t kWideLaunchSets = 262144;
 constexpr uint64_t kWideNodes = 20;
+constexpr int64_t kWideDegree = 8;
+constexpr uint64_t kWideDense = 65536;
 
-// Lanes per set of the IC first tier for a launch of `count` sets on n nodes.
-int launch_lanes(const tim_ctx* c, int64_t n, int model, int mode, uint64_t count) {
-  if (c->wide_small && !c->hub && model == TIM_MODEL_IC &&
-      count < std::min<uint64_t>(kWideLaunchSets, (uint64_t)n / kWideNodes) &&
+// Lanes per set of the IC first tier for a launch of `count` sets on graph g.
+int launch_lanes(const tim_ctx* c, const tim_graph* g, int model, int mode, uint64_t count) {
+  uint64_t few = std::min<uint64_t>(kWideLaunchSets, (uint64_t)g->n / kWideNodes);
+  if (g->m >= kWideDegree * g->n) few = std::max(few, kWideDense);
+  if (c->wide_small && !c->hub && model == TIM_MODEL_IC && count < few &&
       (mode != tim::kModeEmit || c->emit_wave_sets == 0))
     return 64;
   return c->seg_lanes;
 }
 
 // Blocks of the tier-0 sampler over `count` sets (and its wavefronts).
-uint64_t sample_grid(const tim_ctx* c, int64_t n, int model, int mode, bool wc, uint64_t count, uint64_t* waves) {
-  const int lanes = launch_lanes(c, n, model, mode, count);
+uint64_t sample_grid(const tim_ctx* c, const tim_graph* g, int model, int mode, bool wc, uint64_t count, uint64_t* waves) {
+  const int lanes = launch_lanes(c, g, model, mode, count);
   const int per_cu = model == TIM_MODEL_TRIGGER ? c->grid_trig[mode]
                      : model != TIM_MODEL_IC ? c->grid_lt[mode]
                      : lanes == c->seg_lanes ? c->grid_ic[mode][wc ? 1 : 0]
@@ -406,11 +415,11 @@ uint64_t sample_grid(const tim_ctx* c, int64_t n, int model, int mode, bool wc, 
 
 // Wavefronts of the tier-0 launch over `count` sets (the only tier that
 // reserves node-pool slices; the others reserve exactly what they store).
-uint64_t emit_waves(const tim_ctx* c, int64_t n, int model, uint64_t count) {
+uint64_t emit_waves(const tim_ctx* c, const tim_graph* g, int model, uint64_t count) {
   if (c->hub && model != TIM_MODEL_TRIGGER) return c->hub->emit_waves[model];  // any wavefront of a batched launch may visit a job
   uint64_t waves = 0, w2 = 0;
-  sample_grid(c, n, model, tim::kModeEmit, true, count, &waves);
-  sample_grid(c, n, model, tim::kModeEmit, false, count, &w2);
+  sample_grid(c, g, model, tim::kModeEmit, true, count, &waves);
+  sample_grid(c, g, model, tim::kModeEmit, false, count, &w2);
   return std::max(waves, w2);
 }
 
@@ -419,8 +428,8 @@ uint32_t pool_set_cap(const tim_ctx* c) { return c->budget ? tim::kPoolSetCapBud
 
 // Largest set tier 0 stores (its LDS queue or chain) in emit launches of
 // `count` sets.
-uint64_t tier0_cap(const tim_ctx* c, int64_t n, int model, uint64_t count) {
-  const int lanes = launch_lanes(c, n, model, tim::kModeEmit, std::min(count, kMaxLaunchSets));
+uint64_t tier0_cap(const tim_ctx* c, const tim_graph* g, int model, uint64_t count) {
+  const int lanes = launch_lanes(c, g, model, tim::kModeEmit, std::min(count, kMaxLaunchSets));
   const uint32_t cap = tim::tier0_set_cap(model, lanes);
   return model == TIM_MODEL_IC && lanes == 8 ? std::min(cap, pool_set_cap(c)) : cap;
 }
@@ -428,9 +437,9 @@ uint64_t tier0_cap(const tim_ctx* c, int64_t n, int model, uint64_t count) {
 // Node-pool slice for launches of `count` sets holding about `nodes`
 // entries: about a quarter of a wavefront's share, a power of two between
 // four times the largest tier-0 set and max(slice_cap, that).
-uint32_t pick_slice(const tim_ctx* c, int64_t n, int model, uint64_t count, uint64_t nodes) {
-  const uint64_t per_wave = nodes / std::max<uint64_t>(1, emit_waves(c, n, model, std::min(count, kMaxLaunchSets)));
-  const uint32_t lo = (uint32_t)(4 * tier0_cap(c, n, model, count));
+uint32_t pick_slice(const tim_ctx* c, const tim_graph* g, int model, uint64_t count, uint64_t nodes) {
+  const uint64_t per_wave = nodes / std::max<uint64_t>(1, emit_waves(c, g, model, std::min(count, kMaxLaunchSets)));
+  const uint32_t lo = (uint32_t)(4 * tier0_cap(c, g, model, count));
   const uint32_t hi = std::max(lo, c->slice_cap);
   uint32_t s = lo;
   while (s < hi && (uint64_t)s * 8 <= per_wave) s <<= 1;
@@ -442,10 +451,10 @@ uint32_t pick_slice(const tim_ctx* c, int64_t n, int model, uint64_t count, uint
 // less than one set (at most `cap` entries) at a slice boundary, and it
 // crosses a boundary once per slice - cap entries stored plus once more
 // after its last slice, whose rest (at most a slice) is also lost.
-uint64_t pool_need(const tim_ctx* c, int64_t n, int model, uint64_t count, uint64_t nodes, uint32_t slice) {
-  const uint64_t cap = tier0_cap(c, n, model, count);
+uint64_t pool_need(const tim_ctx* c, const tim_graph* g, int model, uint64_t count, uint64_t nodes, uint32_t slice) {
+  const uint64_t cap = tier0_cap(c, g, model, count);
   const uint64_t launches = (count + kMaxLaunchSets - 1) / kMaxLaunchSets;
-  const uint64_t waves = emit_waves(c, n, model, std::min(count, kMaxLaunchSets));
+  const uint64_t waves = emit_waves(c, g, model, std::min(count, kMaxLaunchSets));
   const uint64_t boundary = (nodes * cap + (slice - cap) - 1) / (slice - cap);
   return nodes + boundary + launches * waves * ((uint64_t)slice + cap);
 }
@@ -520,14 +529,14 @@ tim_status sample_launch(tim_ctx* c, const tim_graph* g, int model, int mode, ui
     if (req.st != TIM_OK) return fail(req.st, "%s", req.err.c_str());
     h = req.h;
   } else {
-    const uint64_t grid0 = sample_grid(c, g->n, model, mode, wc, count, nullptr);
+    const uint64_t grid0 = sample_grid(c, g, model, mode, wc, count, nullptr);
     const uint64_t grid1 = (uint64_t)(model == TIM_MODEL_IC        ? c->grid_ic64[mode][wc ? 1 : 0]
                                       : model == TIM_MODEL_TRIGGER ? c->grid_trig1[mode]
                                                                    : c->grid_lt_chain[mode]) *
                            (uint64_t)c->num_cu;
     tim::launch_clear_counters(c->ctr, c->stream);
     if (c->prof_on) HIP_TRY(hipEventRecord(c->pev[0], c->stream));
-    tim::launch_sample(model, mode, a, launch_lanes(c, g->n, model, mode, count), (int)grid0, (int)grid1, c->stream,
+    tim::launch_sample(model, mode, a, launch_lanes(c, g, model, mode, count), (int)grid0, (int)grid1, c->stream,
                        c->prof_on ? c->pev[1] : nullptr);
     if (c->prof_on) HIP_TRY(hipEventRecord(c->pev[2], c->stream));
     HIP_TRY(hipGetLastError());
@@ -552,7 +561,7 @@ tim_status sample_launch(tim_ctx* c, const tim_graph* g, int model, int mode, ui
     HIP_TRY(hipEventElapsedTime(&ms_big, c->pev[1], c->pev[2]));
     // launches in the 64-lane shape are kept apart, so that the sampler[][]
     // entries describe one kernel each
-    tim_kernel_profile& p = (model == TIM_MODEL_IC && launch_lanes(c, g->n, model, mode, count) != c->seg_lanes)
+    tim_kernel_profile& p = (model == TIM_MODEL_IC && launch_lanes(c, g, model, mode, count) != c->seg_lanes)
                                 ? c->prof.ic_wide[mode]
                                 : c->prof.sampler[model][mode];
     const unsigned long long* acc0 = h + tim::kCtrAcc;
@@ -619,8 +628,8 @@ tim_status emit_sets(tim_ctx* c, const tim_graph* g, int model, uint64_t seed, u
   c->stored.valid = false;
   TIM_TRY(ensure(c, c->set_start, count * 8, "set offsets"));
   TIM_TRY(ensure(c, c->set_len, count * 4, "set sizes"));
-  c->slice = pick_slice(c, g->n, model, count, expect_nodes);
-  TIM_TRY(ensure(c, c->pool, pool_need(c, g->n, model, count, std::max<uint64_t>(expect_nodes, 1024), c->slice) * 4,
+  c->slice = pick_slice(c, g, model, count, expect_nodes);
+  TIM_TRY(ensure(c, c->pool, pool_need(c, g, model, count, std::max<uint64_t>(expect_nodes, 1024), c->slice) * 4,
                  "RR node pool"));
   for (int attempt = 0; attempt < 2; ++attempt) {
     Totals t;
@@ -634,7 +643,7 @@ tim_status emit_sets(tim_ctx* c, const tim_graph* g, int model, uint64_t seed, u
       *t_out = t;
       return TIM_OK;
     }
-    TIM_TRY(ensure(c, c->pool, pool_need(c, g->n, model, count, t.nodes, c->slice) * 4, "RR node pool"));
+    TIM_TRY(ensure(c, c->pool, pool_need(c, g, model, count, t.nodes, c->slice) * 4, "RR node pool"));
   }
   return fail(TIM_EDEVICE, "node pool still short after regrowing");
 }
@@ -812,11 +821,12 @@ uint64_t lists_per_set(int model) { return model == TIM_MODEL_IC ? 16 : 8; }
 
 // Peak bytes of the all-resident path for `count` sets of `nodes` entries
 // (node pool, per-set starts and sizes, inverted index).
-uint64_t resident_bytes(const tim_ctx* c, int64_t n, int model, uint64_t count, uint64_t nodes, int k) {
+uint64_t resident_bytes(const tim_ctx* c, const tim_graph* g, int model, uint64_t count, uint64_t nodes, int k) {
   const uint64_t lists = std::min(count, kMaxLaunchSets) * lists_per_set(model);
-  const uint64_t emit = count * 12 + pool_need(c, n, model, count, nodes, pick_slice(c, n, model, count, nodes)) * 4;
-  const uint64_t index = (uint64_t)n * 17 + 8 + nodes * 4 + count + 8 * (uint64_t)k +
-                         tim::scan_temp_bytes((uint64_t)n + 1) + 17 * 256;
+  const uint64_t emit = count * 12 + pool_need(c, g, model, count, nodes, pick_slice(c, g, model, count, nodes)) * 4;
+  const uint64_t n = (uint64_t)g->n;
+  const uint64_t index = n * 17 + 8 + nodes * 4 + count + 8 * (uint64_t)k +
+                         tim::scan_temp_bytes(n + 1) + 17 * 256;
   return lists + emit + index;
 }
 
@@ -857,7 +867,7 @@ tim_status collection_greedy(tim_ctx* c, const tim_graph* g, int model, uint64_t
   uint64_t room = 0;
   TIM_TRY(collection_room(c, &room));
   HIP_TRY(hipEventRecord(c->ev[0], c->stream));
-  if (count <= c->resident_limit && resident_bytes(c, n, model, count, expect_nodes, k) <= room) {
+  if (count <= c->resident_limit && resident_bytes(c, g, model, count, expect_nodes, k) <= room) {
     // the sets stay in the node pool as the samplers left them (no compaction)
     Totals t;
     tim_status s0 = emit_sets(c, g, model, seed, phase, 0, count, expect_nodes, nullptr, &t);
@@ -866,7 +876,7 @@ tim_status collection_greedy(tim_ctx* c, const tim_graph* g, int model, uint64_t
       expect_nodes = std::max(expect_nodes, t.nodes);
       uint64_t room2 = 0;  // counts the buffers the context already holds as usable
       TIM_TRY(collection_room(c, &room2));
-      if (resident_bytes(c, n, model, count, t.nodes, k) <= room2) {
+      if (resident_bytes(c, g, model, count, t.nodes, k) <= room2) {
         HIP_TRY(hipEventRecord(c->ev[1], c->stream));
         st->ms_sample = elapsed_ms(c);
         HIP_TRY(hipEventRecord(c->ev[0], c->stream));
@@ -913,7 +923,7 @@ tim_status collection_greedy(tim_ctx* c, const tim_graph* g, int model, uint64_t
   const uint64_t avail = room - fixed;
   // per chunk set: offsets and size, deferral lists, its nodes with their
   // slice-boundary loss, and its share of the last slices of the wavefronts
-  const double cap = (double)tier0_cap(c, n, model, count), slice = 4.0 * cap;
+  const double cap = (double)tier0_cap(c, g, model, count), slice = 4.0 * cap;
   const double node_bytes = 4.0 * nps * (1.0 + cap / (slice - cap));
   const double slice_per_set = 4.0 * (slice + cap) / (double)c->emit_wave_sets;
   const uint64_t slack_fixed = 4 * (uint64_t)(slice + cap) * 8 + 8 * 256;
@@ -1298,7 +1308,7 @@ tim_status kpt_estimate_impl(tim_ctx* c, const tim_graph* g, int model, uint64_t
       const uint64_t expect = (uint64_t)((double)prev_nodes / (double)prev_c * 1.25 * (double)ci) + 4096;
       uint64_t room = 0;
       TIM_TRY(collection_room(c, &room));
-      if (resident_bytes(c, g->n, model, ci, expect, k) + ci * 4 <= room) {
+      if (resident_bytes(c, g, model, ci, expect, k) + ci * 4 <= room) {
         struct KappaScope {
           tim_ctx* c;
           ~KappaScope() { c->emit_kappa_k = 0; }
@@ -1310,7 +1320,7 @@ tim_status kpt_estimate_impl(tim_ctx* c, const tim_graph* g, int model, uint64_t
           // RefineKPT's index fits beside them (if not, RefineKPT generates R' again)
           uint64_t room2 = 0;
           TIM_TRY(collection_room(c, &room2));
-          stored = resident_bytes(c, g->n, model, ci, t.nodes, k) <= room2;
+          stored = resident_bytes(c, g, model, ci, t.nodes, k) <= room2;
           counted = true;
           if (!stored) release_transients(c);
         } else if (es == TIM_EBUDGET) {
@@ -1481,7 +1491,7 @@ tim_status run_impl(tim_ctx* c, const tim_graph* g, int model, int k, double eps
     const uint64_t expect = (uint64_t)(mean_nodes * 1.25 * (double)theta) + 4096;
     SelectTimes times;
     uint64_t grant = 0;
-    if (c->hub) grant = hub_admit(c, resident_bytes(c, g->n, model, theta, expect, k) + theta * 8);
+    if (c->hub) grant = hub_admit(c, resident_bytes(c, g, model, theta, expect, k) + theta * 8);
     st = node_select_impl(c, g, model, seed, k, theta, expect, seeds, gains, &r->select, &times);
     if (c->hub) hub_return(c, grant);
     if (st == TIM_OK) {
