@@ -751,10 +751,11 @@ __global__ __launch_bounds__(kThreads) void scan_cover_kernel(const unsigned lon
 
 // ---- the greedy over candidates ----
 //
-// Counts only fall, so a node whose initial count is below T is never chosen
-// while some candidate (initial count at least T) still has T or more.  The
-// greedy of k > 1 therefore takes the nodes of the largest counts as
-// candidates (kCandPerStep per step, at least kCandMin, at most kCandMax) and
+// A choice's key is its count, ties to the lowest node.  Counts only fall, so a
+// node whose initial key is below T is never chosen while some candidate
+// (initial key at least T) still has T or more.  The greedy of k > 1 therefore
+// takes the nodes of the largest keys as candidates (kCandPerStep per step, at
+// least kCandMin, at most kCandMax) and
 // keeps of every set only its candidates, as a stream of 16-bit candidate
 // numbers whose top bit marks the first entry of a set.  One kernel over the
 // stream takes one or several greedy steps: every block decides them itself from
@@ -768,7 +769,7 @@ __global__ __launch_bounds__(kThreads) void scan_cover_kernel(const unsigned lon
 // choice follow from the combinations, and the best of them is the next choice as
 // long as its key is above that of every candidate outside the tops (their counts
 // only fall).
-// A launch whose best candidate has fallen below T leaves key 1, which no choice
+// A launch whose best candidate's key has fallen below T leaves key 1, which no choice
 // has, and the caller runs the greedy over all nodes.  Seeds and gains are those
 // of that greedy: a choice's key is the largest over all nodes at its step.
 // Against the inverted index with an argmax over n nodes and a cover pass per
@@ -786,8 +787,9 @@ constexpr int kCandMaxSteps = 256;   // beyond, the candidates a greedy needs ou
 constexpr uint32_t kCandDead = 0x7FFFu;      // number of an entry taken out
 constexpr uint32_t kCandFirst = 0x8000u;     // first entry of its set
 constexpr uint32_t kCandTaken = 0xFFFFFFFFu; // count of a chosen candidate
-constexpr int kCandBins = 1024;
-constexpr uint32_t kCandBinsUsed = 128u + 25u * 16u;  // those above belong to no 32-bit count
+constexpr int kCandBins = 2048;
+constexpr uint32_t kCandBinsUsed = 128u + 25u * 64u;  // those above belong to no 32-bit count
+constexpr uint32_t kCandTies = 32;   // counts whose nodes are also counted per block: T may lie between equal counts
 constexpr int kCandSegs = 256;       // parts of the stream, one per block of a step
 constexpr int kCandStepThreads = 1024;
 constexpr int kCandBuildThreads = 1024;
@@ -802,8 +804,8 @@ constexpr uint32_t kCandOpen = 0x200u;    // with them: the set goes on after th
 constexpr uint32_t kCandStarts = 1u << 24;
 
 struct CandHead {  // counters of one greedy
+  unsigned long long t;  // T, as a key
   uint32_t n;      // candidates
-  uint32_t t;      // T
   uint32_t cursor; // stream entries reserved
   uint32_t failed; // a step found no candidate at or above T
   uint32_t picked[2];  // choices before launches j mod 2
@@ -824,16 +826,22 @@ struct CandArrays {
   int segs;
 };
 
-// Bins of counts: exact below 128, then 16 per power of two.
+// Bins of counts: exact below 128, then 64 per power of two (the more alike the
+// counts are, the finer the bins have to be to part the largest from the rest).
 __device__ __forceinline__ uint32_t cand_bin(uint32_t c) {
   if (c < 128u) return c;
   const uint32_t e = 31u - (uint32_t)__clz((int)c);
-  return 128u + (e - 7u) * 16u + ((c >> (e - 4u)) & 15u);
+  return 128u + (e - 7u) * 64u + ((c >> (e - 6u)) & 63u);
 }
 __device__ __forceinline__ uint32_t cand_bin_low(uint32_t b) {
   if (b < 128u) return b;
-  const uint32_t e = 7u + (b - 128u) / 16u;
-  return (16u + ((b - 128u) & 15u)) << (e - 4u);
+  const uint32_t e = 7u + (b - 128u) / 64u;
+  return (64u + ((b - 128u) & 63u)) << (e - 6u);
+}
+
+// Nodes per block of cand_bins_kernel and cand_pick_kernel, which have the same grid.
+__device__ __forceinline__ int64_t cand_span(int64_t n) {
+  return ((n + gridDim.x - 1) / gridDim.x + kThreads - 1) / kThreads * kThreads;
 }
 
 // Clears the counters, bins and dec, and marks every candidate number of
@@ -847,13 +855,15 @@ __global__ void cand_init_kernel(CandArrays c, unsigned long long* best, int k) 
   for (int x = i; x < 2 * kCandMax; x += stride) c.base[x] = kCandTaken;
 }
 
-__global__ __launch_bounds__(kThreads) void cand_bins_kernel(const uint32_t* cnt, int64_t n, uint32_t* bins) {
+// ties[b * kCandTies + c]: nodes of block b with count c.
+__global__ __launch_bounds__(kThreads) void cand_bins_kernel(const uint32_t* cnt, int64_t n, uint32_t* bins,
+                                                             uint32_t* ties) {
   __shared__ uint32_t s_bin[kCandBins];
   for (int i = threadIdx.x; i < kCandBins; i += kThreads) s_bin[i] = 0u;
   __syncthreads();
   uint32_t low[4] = {0u, 0u, 0u, 0u};  // most nodes have counts below 4: not through one LDS word
-  const int64_t stride = (int64_t)gridDim.x * kThreads;
-  for (int64_t u = (int64_t)blockIdx.x * kThreads + threadIdx.x; u < n; u += stride) {
+  const int64_t lo = (int64_t)blockIdx.x * cand_span(n), hi = min(lo + cand_span(n), n);
+  for (int64_t u = lo + threadIdx.x; u < hi; u += kThreads) {
     const uint32_t c = cnt[u];
     if (c >= 4u) atomicAdd(&s_bin[cand_bin(c)], 1u);
 #pragma unroll
@@ -869,14 +879,22 @@ __global__ __launch_bounds__(kThreads) void cand_bins_kernel(const uint32_t* cnt
   __syncthreads();
   for (int i = threadIdx.x; i < kCandBins; i += kThreads)
     if (s_bin[i]) atomicAdd(&bins[i], s_bin[i]);
+  if (threadIdx.x < kCandTies) ties[(size_t)blockIdx.x * kCandTies + threadIdx.x] = s_bin[threadIdx.x];
 }
 
-// T: the low end of the lowest bin with at most `most` nodes in it and above
-// (0 where all n nodes are at most that), then the candidates' numbers.
+// T: the low end of the lowest bin with at most `most` nodes in it and above.
+// Of the next lower bin, if all its nodes have one small count, the blocks from
+// the first on join as long as their nodes of that count fit, so that equal
+// counts do not end the greedy early: T is then the key of the last node of the
+// last such block.  (0 where all n nodes are candidates.)  Then the candidates'
+// numbers.  Neighbouring nodes get numbers 64 apart, in different rows of lanes
+// of a step, which takes its next tops from the best of each row: nodes of the
+// largest keys that are numbered one after the other would leave it one choice
+// per launch (graphs whose hubs come first, equal counts).
 __global__ __launch_bounds__(kThreads) void cand_pick_kernel(const uint32_t* cnt, int64_t n, uint32_t most,
-                                                             CandArrays c) {
+                                                             const uint32_t* ties, CandArrays c) {
   __shared__ unsigned long long red[kThreads / 64];
-  __shared__ uint32_t s_t;
+  __shared__ uint32_t s_cut, s_above;
   constexpr int per = kCandBins / kThreads;
   // thread t holds bins from the top: kCandBins - 1 - per * t downwards
   uint32_t b[per];
@@ -886,35 +904,60 @@ __global__ __launch_bounds__(kThreads) void cand_pick_kernel(const uint32_t* cnt
     b[i] = c.bins[kCandBins - 1 - per * (int)threadIdx.x - i];
     sum += b[i];
   }
-  if (threadIdx.x == 0) s_t = 0xFFFFFFFFu;  // the top bin alone is too large
-  unsigned long long above = block_excl_scan(sum, red, &total);
+  if (threadIdx.x == 0) {
+    s_cut = kCandBinsUsed;  // the top bin alone is too large
+    s_above = 0u;
+  }
+  const unsigned long long before = block_excl_scan(sum, red, &total);
+  unsigned long long above = before;
 #pragma unroll
   for (int i = 0; i < per; ++i) {
     above += b[i];
     const uint32_t bin = (uint32_t)(kCandBins - 1 - per * (int)threadIdx.x - i);
-    if (above <= most && bin < kCandBinsUsed) atomicMin(&s_t, cand_bin_low(bin));
+    if (above <= most && bin < kCandBinsUsed) atomicMin(&s_cut, bin);
   }
   __syncthreads();
-  const uint32_t t = n <= (int64_t)most ? 0u : s_t;
+  const uint32_t cut = s_cut;
+  above = before;
+#pragma unroll
+  for (int i = 0; i < per; ++i) {
+    above += b[i];
+    if ((uint32_t)(kCandBins - 1 - per * (int)threadIdx.x - i) == cut) s_above = (uint32_t)above;
+  }
   __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x == 0) c.head->t = t;
+  const bool all = n <= (int64_t)most;
+  const uint32_t t = all ? 0u : cut < kCandBinsUsed ? cand_bin_low(cut) : 0xFFFFFFFFu;
+  const int64_t span = cand_span(n);
+  int64_t joined = 0;  // nodes below this one of count t - 1 are candidates too
+  if (!all && cut <= kCandTies) {  // (cut > 0: all bins together hold n nodes)
+    const unsigned long long mine = threadIdx.x < gridDim.x ? ties[(size_t)threadIdx.x * kCandTies + cut - 1u] : 0ull;
+    const unsigned long long upto = block_excl_scan(mine, red, &total) + mine;
+    joined = span * (int64_t)block_sum_u64(threadIdx.x < gridDim.x && s_above + upto <= most ? 1ull : 0ull, red);
+    joined = min(joined, n);
+  }
+  __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    c.head->t = t == 0xFFFFFFFFu ? ~0ull : ((unsigned long long)t << 32) - (unsigned long long)joined;
   // the block's nodes in two passes, so that it reserves its candidates' numbers with one atomic
-  const int64_t span = ((n + gridDim.x - 1) / gridDim.x + kThreads - 1) / kThreads * kThreads;
   const int64_t lo = (int64_t)blockIdx.x * span, hi = min(lo + span, n);
+  const uint32_t least = lo < joined ? t - 1u : t;  // joined is a block's first node, or n
   unsigned long long mine = 0;
-  for (int64_t u = lo + threadIdx.x; u < hi; u += kThreads) mine += cnt[u] >= t ? 1ull : 0ull;
+  for (int64_t u = lo + threadIdx.x; u < hi; u += kThreads) mine += cnt[u] >= least ? 1ull : 0ull;
   uint32_t id = (uint32_t)block_excl_scan(mine, red, &total);
-  if (threadIdx.x == 0) s_t = total ? atomicAdd(&c.head->n, (uint32_t)total) : 0u;
+  if (threadIdx.x == 0) s_cut = total ? atomicAdd(&c.head->n, (uint32_t)total) : 0u;
   __syncthreads();
-  id += s_t;
+  id += s_cut;
+  const uint32_t rows = most / 64u;
   for (int64_t u = lo + threadIdx.x; u < hi; u += kThreads) {
     const uint32_t x = cnt[u];
-    const bool in = x >= t;
+    const bool in = x >= least;
+    const uint32_t num = id % rows * 64u + id / rows;
     if (in) {
-      c.node[id] = (uint32_t)u;
-      c.base[id] = x;
+      c.node[num] = (uint32_t)u;
+      c.base[num] = x;
     }
-    c.map[u] = in ? (uint16_t)++id : (uint16_t)0u;
+    c.map[u] = in ? (uint16_t)(num + 1u) : (uint16_t)0u;
+    id += in ? 1u : 0u;
   }
 }
 
@@ -1133,7 +1176,8 @@ __global__ __launch_bounds__(kCandStepThreads) void cand_step_kernel(CandArrays 
   __shared__ int s_open[2];
   const int tid = threadIdx.x, lane = tid % 64, wv = tid / 64;
   CandHead* head = c.head;
-  const uint32_t t = head->t, picked = head->picked[j & 1];
+  const unsigned long long t = head->t;
+  const uint32_t picked = head->picked[j & 1];
   const bool failed = head->failed != 0u;
   const int nvec = (int)(c.seg_len[blockIdx.x] / 8u);
   uint16_t* part = c.stream + c.seg_start[blockIdx.x];
@@ -1272,7 +1316,7 @@ __global__ __launch_bounds__(kCandStepThreads) void cand_step_kernel(CandArrays 
     unsigned long long top = lane64(row_max64(in), 0);
     int n = 0;
     if (bound >= top) {
-      if (bound != 0ull && (uint32_t)(bound >> 32) >= t) {
+      if (bound != 0ull && bound >= t) {
         if (s_key[lane] == bound) s_chosen[0] = s_num[lane];
         if (lane == 0 && blockIdx.x == 0) best[picked] = bound;
         n = 1;
@@ -1281,7 +1325,7 @@ __global__ __launch_bounds__(kCandStepThreads) void cand_step_kernel(CandArrays 
       const uint32_t low = (uint32_t)in;
       uint32_t left = kCandCombos - 1;      // the tops not chosen
       bool is_left = in != 0ull;
-      while (top > bound && (uint32_t)(top >> 32) >= t && picked + (uint32_t)n < (uint32_t)k) {
+      while (top > bound && top >= t && picked + (uint32_t)n < (uint32_t)k) {
         const uint64_t who = __ballot(in == top && is_left);
         const int i = __ffsll((unsigned long long)who) - 1;
         if (lane == i) {
@@ -1705,8 +1749,11 @@ void cand_prepare(const GreedyArgs& a, V sets, hipStream_t s) {
   hipLaunchKernelGGL(cand_init_kernel, dim3(16), dim3(kThreads), 0, s, c, a.best, a.k);
   const unsigned grid = grid_for((uint64_t)a.n, 256);
   const int most = cand_most(a);
-  if (a.n > most) hipLaunchKernelGGL(cand_bins_kernel, dim3(grid), dim3(kThreads), 0, s, a.cnt, a.n, c.bins);
-  hipLaunchKernelGGL(cand_pick_kernel, dim3(grid), dim3(kThreads), 0, s, a.cnt, a.n, (uint32_t)most, c);
+  // the nodes of small counts per block lie where the stream is built after that (it has 64 entries per part to spare)
+  static_assert((size_t)kThreads * kCandTies * 4 <= 64 * (size_t)kCandSegs * 2, "a grid of kThreads blocks fits");
+  uint32_t* ties = reinterpret_cast<uint32_t*>(c.stream);
+  if (a.n > most) hipLaunchKernelGGL(cand_bins_kernel, dim3(grid), dim3(kThreads), 0, s, a.cnt, a.n, c.bins, ties);
+  hipLaunchKernelGGL(cand_pick_kernel, dim3(grid), dim3(kThreads), 0, s, a.cnt, a.n, (uint32_t)most, ties, c);
   // tiles of about two windows' entries, at least one per block
   const uint64_t mean = a.total / a.nsets + 1;
   const uint64_t ts = std::min<uint64_t>(2 * kCandWindow / mean, a.nsets / (uint64_t)c.segs + 1);
