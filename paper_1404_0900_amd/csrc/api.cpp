@@ -2711,6 +2711,8 @@ tim_status tim_spread_mc(tim_ctx* c, const tim_graph* g, int model, uint64_t see
   a.runs = runs;
   a.seeds = c->rr_nodes.as<int32_t>();
   a.nseeds = nseeds;
+  a.list_cap = (uint32_t)std::min<uint64_t>(runs, 1u << 16);
+  if (ensure(c, c->list1, (size_t)a.list_cap * 8, "large runs") == TIM_OK) a.list = c->list1.as<uint64_t>();
   a.counts = d_counts;
   a.ctr = c->ctr;
   a.stamp = c->big_stamp.as<uint32_t>();

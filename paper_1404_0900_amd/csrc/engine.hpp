@@ -215,7 +215,10 @@ struct SpreadArgs {
   const int32_t* seeds;       // nseeds node ids (repeats allowed)
   int nseeds;
   uint32_t* counts;           // per run, nullable
-  unsigned long long* ctr;    // [0] run cursor, [1] sum of the runs' spreads (cleared by the caller)
+  unsigned long long* ctr;    // [0] run cursor, [1] sum of the runs' spreads, [2] length of the list, [3] cursor over it
+                              // (cleared by the caller)
+  uint64_t* list;             // runs that the first of two launches leaves to the second (list_cap of them), nullable
+  uint32_t list_cap;
   uint32_t* stamp;            // per slot: n stamps and an n-entry queue, stride entries apart
   int32_t* queue;
   uint32_t* epoch;

@@ -116,7 +116,22 @@ __device__ __forceinline__ bool out_edge_live(const GraphView& g, const Key& key
 // instead of four change that by 1 to 8%.
 constexpr int kSpreadLoads = 4;
 
-template <int MODEL, int WORDS, int T>
+// A bitmap of more than 8192 words leaves a CU one or two blocks, and a run of a
+// few nodes, a chain of latencies, keeps a block as long as it takes whatever the
+// block's size: 20000 LT runs of one seed (3.8 nodes each) on 1M nodes took 0.36
+// ms with four blocks of stamps per CU and 0.64 ms with one bitmap.  Runs on such
+// graphs therefore start with stamps (pass 1), and one that visits more than
+// kSpreadFewNodes nodes besides its seeds, or is about to take more than
+// kSpreadFewEdges out-edges at once, goes to a list for the bitmap (pass 2): the
+// runs above take 0.37 ms, 50000 runs of one seed on 400K nodes 0.66 (0.66 with
+// stamps, 0.83 with the bitmap), 1000 runs of 50 hubs on 1M nodes 31.4 (139 and
+// 31.3), 1000 runs of 50 random seeds (200 nodes) 0.53 (2.8 and 0.49).  With 256
+// nodes or 4096 edges the last become 0.57, with 256 edges 5000 runs of 53 nodes
+// take 0.33 instead of 0.15.
+constexpr uint32_t kSpreadFewNodes = 64, kSpreadFewEdges = 1024;
+
+// PASS: 0: all runs here; 1: large runs go to the list; 2: the runs are those of the list.
+template <int MODEL, int WORDS, int T, int PASS>
 __global__ __launch_bounds__(T) void spread_kernel(SpreadArgs a) {
   constexpr int NW = T / kWave;
   constexpr uint32_t W = 16u * T;    // edges per window
@@ -137,6 +152,7 @@ __global__ __launch_bounds__(T) void spread_kernel(SpreadArgs a) {
   int32_t* queue = a.queue + (size_t)slot * (size_t)a.stride;
   const int nwords = WORDS ? (int)((g.n + 31) >> 5) : 0;  // at most WORDS (launch_spread)
   const uint64_t upto = ~0ull >> (63 - lane);             // lanes up to this one
+  const unsigned long long todo = PASS == 2 ? min(a.ctr[2], (unsigned long long)a.list_cap) : a.runs;
   unsigned long long total = 0;
   uint32_t ep = 0;
 
@@ -154,15 +170,16 @@ __global__ __launch_bounds__(T) void spread_kernel(SpreadArgs a) {
 
   for (;;) {
     if (tid == 0) {
-      s_idx = atomicAdd(&a.ctr[0], 1ull);
+      s_idx = atomicAdd(&a.ctr[PASS == 2 ? 3 : 0], 1ull);
       if (!WORDS) s_epoch = a.epoch[slot] + 1u;
       s_tail = 0u;
     }
     if (WORDS)
       for (int i = tid; i < nwords; i += T) s_bits[i] = 0u;
     __syncthreads();
-    const unsigned long long idx = s_idx;
-    if (idx >= a.runs) break;
+    unsigned long long idx = s_idx;
+    if (idx >= todo) break;
+    if (PASS == 2) idx = a.list[idx];
     if (!WORDS) {
       ep = s_epoch;
       if (ep == 0u) {  // stamp counter wrapped: start the slot afresh
@@ -183,6 +200,7 @@ __global__ __launch_bounds__(T) void spread_kernel(SpreadArgs a) {
     }
     __syncthreads();
     uint32_t head = 0;
+    bool few = PASS == 1, listed = false;  // few: a run that turns out large goes to the list
     for (;;) {
       const uint32_t tail = s_tail;
       if (head >= tail) break;
@@ -207,6 +225,18 @@ __global__ __launch_bounds__(T) void spread_kernel(SpreadArgs a) {
         all += s_wtot[w];
       }
       const uint32_t items = (uint32_t)(all & ((1ull << 40) - 1ull));  // at most m < 2^32
+      if (PASS == 1 && few && (tail > (uint32_t)a.nseeds + kSpreadFewNodes || items > kSpreadFewEdges)) {
+        __syncthreads();
+        if (tid == 0) s_idx = atomicAdd(&a.ctr[2], 1ull);
+        __syncthreads();
+        const unsigned long long at = s_idx;
+        if (at < (unsigned long long)a.list_cap) {
+          if (tid == 0) a.list[at] = idx;
+          listed = true;
+          break;
+        }
+        few = false;  // no room: it is finished here
+      }
       const uint32_t first_edge = (uint32_t)(before & ((1ull << 40) - 1ull));
       if (d) s_delta[(uint32_t)(before >> 40)] = ea - first_edge;
       head += (uint32_t)nb;
@@ -275,7 +305,7 @@ __global__ __launch_bounds__(T) void spread_kernel(SpreadArgs a) {
       }
       __syncthreads();
     }
-    if (tid == 0) {
+    if (tid == 0 && !listed) {
       const uint32_t cnt = s_tail;
       if (a.counts) a.counts[idx] = cnt;
       total += cnt;
@@ -301,9 +331,9 @@ namespace {
 
 // Blocks of the variant that fit a CU by its LDS and 2048 threads, over the
 // whole chip, but no more than there are slots or runs.
-template <int MODEL, int WORDS, int T>
-void launch_spread_as(const SpreadArgs& a, hipStream_t s) {
-  const void* k = reinterpret_cast<const void*>(spread_kernel<MODEL, WORDS, T>);
+template <int MODEL, int WORDS, int T, int PASS>
+uint64_t spread_blocks() {
+  const void* k = reinterpret_cast<const void*>(spread_kernel<MODEL, WORDS, T, PASS>);
   int per_cu = 0, dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1 ||
@@ -311,8 +341,13 @@ void launch_spread_as(const SpreadArgs& a, hipStream_t s) {
     (void)hipGetLastError();
     per_cu = cus = 1 << 10;  // the slots then bound the grid
   }
-  const uint64_t grid = std::min<uint64_t>({(uint64_t)per_cu * (uint64_t)cus, (uint64_t)a.slots, a.runs});
-  hipLaunchKernelGGL((spread_kernel<MODEL, WORDS, T>), dim3((unsigned)std::max<uint64_t>(grid, 1)), dim3(T), 0, s, a);
+  return (uint64_t)per_cu * (uint64_t)cus;
+}
+
+template <int MODEL, int WORDS, int T, int PASS = 0>
+void launch_spread_as(const SpreadArgs& a, hipStream_t s) {
+  const uint64_t grid = std::min<uint64_t>({spread_blocks<MODEL, WORDS, T, PASS>(), (uint64_t)a.slots, a.runs});
+  hipLaunchKernelGGL((spread_kernel<MODEL, WORDS, T, PASS>), dim3((unsigned)std::max<uint64_t>(grid, 1)), dim3(T), 0, s, a);
 }
 
 // The smallest LDS bitmap that holds n nodes: the less LDS a block takes, the
@@ -322,13 +357,24 @@ void launch_spread_as(const SpreadArgs& a, hipStream_t s) {
 // 256-thread blocks); larger bitmaps leave room for one or two blocks, so those
 // have 1024 threads, up to the 1.2M nodes whose bitmap takes most of a CU's
 // 160 KB.  Larger graphs keep stamps in device memory.
+// The two passes above, where there are more runs than the bitmap's blocks hold at once.
+template <int MODEL, int WORDS, int T>
+void launch_spread_large(const SpreadArgs& a, hipStream_t s) {
+  if (!a.list || std::min<uint64_t>(a.runs, (uint64_t)a.slots) <= spread_blocks<MODEL, WORDS, T, 0>()) {
+    launch_spread_as<MODEL, WORDS, T>(a, s);
+    return;
+  }
+  launch_spread_as<MODEL, 0, 512, 1>(a, s);
+  launch_spread_as<MODEL, WORDS, T, 2>(a, s);
+}
+
 template <int MODEL>
 void launch_spread_model(const SpreadArgs& a, hipStream_t s) {
   const int64_t words = (a.g.n + 31) >> 5;
   if (words <= 2048) launch_spread_as<MODEL, 2048, 512>(a, s);
   else if (words <= 8192) launch_spread_as<MODEL, 8192, 512>(a, s);
-  else if (words <= 16384) launch_spread_as<MODEL, 16384, 1024>(a, s);
-  else if (words <= kSpreadMaxWords) launch_spread_as<MODEL, kSpreadMaxWords, 1024>(a, s);
+  else if (words <= 16384) launch_spread_large<MODEL, 16384, 1024>(a, s);
+  else if (words <= kSpreadMaxWords) launch_spread_large<MODEL, kSpreadMaxWords, 1024>(a, s);
   else launch_spread_as<MODEL, 0, 512>(a, s);
 }
 
