@@ -56,9 +56,13 @@ import hashlib
 KS = (1, 10, 50)
 EPS, ELL, SEED = 0.2, 1.0, 2
 HBM_PEAK_GBS = 8000.0
-# Algorithmic bytes per RR entry of the inverted index and greedy: the entry read by the counts pass, read and
-# written by the scatter, and read by the cover pass that decrements the counts of a chosen node's sets (4 B each).
-GREEDY_BYTES_PER_ENTRY = 20
+# Bytes that the counts and the greedy cannot do without, whatever passes run: every RR entry (4 B) is read once for the
+# counts and, for k > 1, once more when the counts have shown which nodes matter; every node's count is written and read.
+# The passes move more (the counting sort also writes and reads the entries of large collections).
+def greedy_bytes(entries, k, n):
+    return (4 if k == 1 else 8) * entries + 8 * n
+
+
 SEG_GROUPS = 1  # 4-edge groups per lane and step of the IC segment kernels (kSegGroups)
 MODES = ("widths", "store", "cover")
 # HBM bytes per launch of the first-tier IC kernels that can be the dominant
@@ -176,7 +180,7 @@ def main():
     torch.cuda.synchronize()
     eng.profile(True)
     sets = width = 0
-    greedy_entries = greedy_argmax_bytes = 0  # RR entries the greedy runs index, and their argmax passes' bytes
+    greedy_entries = ig_bytes = 0  # RR entries of the greedy runs, and their bytes
     per_k = {k: 0.0 for k in KS}
     t0 = time.perf_counter()
     for i in range(args.steps):
@@ -184,8 +188,9 @@ def main():
             sets += rep.sets_total
             width += rep.width_total
             # two greedy runs per query: RefineKPT's on R' (the last KptEstimation round) and NodeSelection's
-            greedy_entries += int(rep.kpt.round_nodes[rep.kpt.i_last]) + int(rep.select.nodes)
-            greedy_argmax_bytes += 2 * k * 4 * g.n
+            for entries in (int(rep.kpt.round_nodes[rep.kpt.i_last]), int(rep.select.nodes)):
+                greedy_entries += entries
+                ig_bytes += greedy_bytes(entries, k, g.n)
             per_k[k] += dt
             phases[str(k)] = {"kpt_ms": round(rep.ms_kpt, 3), "refine_ms": round(rep.ms_refine, 3),
                               "select_sample_ms": round(rep.ms_select_sample, 3),
@@ -223,14 +228,13 @@ def main():
     if roofline_widths:
         roofline_widths["kernel"] = listed_kernel(roofline_widths["kernel"])
     ig_ms = prof.index_ms + prof.greedy_ms
-    ig_bytes = GREEDY_BYTES_PER_ENTRY * greedy_entries + greedy_argmax_bytes
     ig_gbs = ig_bytes / (ig_ms * 1e-3) / 1e9 if ig_ms > 0 else 0.0
     roofline_index_greedy = {
         "bound": "hbm", "achieved": round(ig_gbs, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": round(ig_gbs / HBM_PEAK_GBS, 5), "traffic": None,
         "kernels": "counts, candidate stream or inverted index, and greedy steps of every query",
-        "entries_per_step": greedy_entries // args.steps, "bytes_per_entry": GREEDY_BYTES_PER_ENTRY,
-        "argmax_bytes_per_step": greedy_argmax_bytes // args.steps, "gpu_ms_per_step": round(ig_ms / args.steps, 3)}
+        "entries_per_step": greedy_entries // args.steps, "bytes_per_step": ig_bytes // args.steps,
+        "index_builds": int(prof.index_calls) // args.steps, "gpu_ms_per_step": round(ig_ms / args.steps, 3)}
 
     line = {
         "metric": "RR sets/s (IC, 1 GPU, TIM+ on 1M-node Chung-Lu, k in {1,10,50})",

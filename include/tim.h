@@ -225,7 +225,8 @@ typedef struct {
 
 typedef struct {
   tim_kernel_profile sampler[2][3]; /* [model][0: widths, 1: stored sets, 2: coverage] */
-  uint64_t index_calls;             /* inverted-index builds + greedy runs */
+  uint64_t index_calls;             /* greedy runs with the counts and index they work on; one whose candidates do not
+                                       decide every step runs again over all nodes and counts twice */
   double index_ms, greedy_ms;
   tim_kernel_profile ic_wide[3];    /* IC launches of few sets (fewer than n / 20 and 262144; with 8 edges per
                                        node or more fewer than 65536 at least), which run the 64-lane first

@@ -896,58 +896,59 @@ __global__ __launch_bounds__(kThreads) void cand_pick_kernel(const uint32_t* cnt
   __shared__ unsigned long long red[kThreads / 64];
   __shared__ uint32_t s_cut, s_above;
   constexpr int per = kCandBins / kThreads;
-  // thread t holds bins from the top: kCandBins - 1 - per * t downwards
-  uint32_t b[per];
-  unsigned long long sum = 0, total;
-#pragma unroll
-  for (int i = 0; i < per; ++i) {
-    b[i] = c.bins[kCandBins - 1 - per * (int)threadIdx.x - i];
-    sum += b[i];
-  }
-  if (threadIdx.x == 0) {
-    s_cut = kCandBinsUsed;  // the top bin alone is too large
-    s_above = 0u;
-  }
-  const unsigned long long before = block_excl_scan(sum, red, &total);
-  unsigned long long above = before;
-#pragma unroll
-  for (int i = 0; i < per; ++i) {
-    above += b[i];
-    const uint32_t bin = (uint32_t)(kCandBins - 1 - per * (int)threadIdx.x - i);
-    if (above <= most && bin < kCandBinsUsed) atomicMin(&s_cut, bin);
-  }
-  __syncthreads();
-  const uint32_t cut = s_cut;
-  above = before;
-#pragma unroll
-  for (int i = 0; i < per; ++i) {
-    above += b[i];
-    if ((uint32_t)(kCandBins - 1 - per * (int)threadIdx.x - i) == cut) s_above = (uint32_t)above;
-  }
-  __syncthreads();
-  const bool all = n <= (int64_t)most;
-  const uint32_t t = all ? 0u : cut < kCandBinsUsed ? cand_bin_low(cut) : 0xFFFFFFFFu;
+  static_assert(per == 8, "two loads of four bins per thread");
   const int64_t span = cand_span(n);
+  unsigned long long total;
+  uint32_t t = 0;
   int64_t joined = 0;  // nodes below this one of count t - 1 are candidates too
-  if (!all && cut <= kCandTies) {  // (cut > 0: all bins together hold n nodes)
-    const unsigned long long mine = threadIdx.x < gridDim.x ? ties[(size_t)threadIdx.x * kCandTies + cut - 1u] : 0ull;
-    const unsigned long long upto = block_excl_scan(mine, red, &total) + mine;
-    joined = span * (int64_t)block_sum_u64(threadIdx.x < gridDim.x && s_above + upto <= most ? 1ull : 0ull, red);
-    joined = min(joined, n);
+  if (n > (int64_t)most) {
+    // thread t holds bins from the top: kCandBins - 1 - per * t downwards
+    const uint32_t top = (uint32_t)(kCandBins - 1 - per * (int)threadIdx.x);
+    const uint4* b4 = reinterpret_cast<const uint4*>(c.bins) + (top + 1u - (uint32_t)per) / 4u;
+    const uint4 b0 = b4[0], b1 = b4[1];
+    const uint32_t b[per] = {b1.w, b1.z, b1.y, b1.x, b0.w, b0.z, b0.y, b0.x};
+    if (threadIdx.x == 0) {
+      s_cut = kCandBinsUsed;  // the top bin alone is too large
+      s_above = 0u;
+    }
+    unsigned long long above = block_excl_scan((unsigned long long)(b[0] + b[1] + b[2] + b[3] + b[4] + b[5] + b[6] + b[7]),
+                                               red, &total);
+    uint32_t cut_here = kCandBinsUsed, above_here = 0;
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+      above += b[i];
+      if (above <= most && top - (uint32_t)i < kCandBinsUsed) {
+        cut_here = top - (uint32_t)i;
+        above_here = (uint32_t)above;
+      }
+    }
+    if (cut_here < kCandBinsUsed) atomicMin(&s_cut, cut_here);
+    __syncthreads();
+    const uint32_t cut = s_cut;
+    if (cut_here == cut && cut < kCandBinsUsed) s_above = above_here;
+    t = cut < kCandBinsUsed ? cand_bin_low(cut) : 0xFFFFFFFFu;
+    if (cut <= kCandTies) {  // (cut > 0: all bins together hold n nodes)
+      const bool block = threadIdx.x < gridDim.x;
+      const unsigned long long mine = block ? ties[(size_t)threadIdx.x * kCandTies + cut - 1u] : 0ull;
+      const unsigned long long upto = block_excl_scan(mine, red, &total) + mine;
+      joined = min(span * (int64_t)__syncthreads_count(block && s_above + upto <= most), n);
+    }
+    __syncthreads();
   }
-  __syncthreads();
   if (blockIdx.x == 0 && threadIdx.x == 0)
     c.head->t = t == 0xFFFFFFFFu ? ~0ull : ((unsigned long long)t << 32) - (unsigned long long)joined;
   // the block's nodes in two passes, so that it reserves its candidates' numbers with one atomic
   const int64_t lo = (int64_t)blockIdx.x * span, hi = min(lo + span, n);
   const uint32_t least = lo < joined ? t - 1u : t;  // joined is a block's first node, or n
   unsigned long long mine = 0;
+#pragma unroll 4
   for (int64_t u = lo + threadIdx.x; u < hi; u += kThreads) mine += cnt[u] >= least ? 1ull : 0ull;
   uint32_t id = (uint32_t)block_excl_scan(mine, red, &total);
   if (threadIdx.x == 0) s_cut = total ? atomicAdd(&c.head->n, (uint32_t)total) : 0u;
   __syncthreads();
   id += s_cut;
   const uint32_t rows = most / 64u;
+#pragma unroll 4
   for (int64_t u = lo + threadIdx.x; u < hi; u += kThreads) {
     const uint32_t x = cnt[u];
     const bool in = x >= least;
@@ -1955,7 +1956,7 @@ void launch_set_u64(unsigned long long* p, unsigned long long v, hipStream_t s) 
 void launch_greedy(const GreedyArgs& a, int k, hipStream_t s) {
   if (use_candidates(a)) {
     const CandArrays c = cand_arrays(a);
-    for (int j = a.launched; j < a.launched + cand_launches(k); ++j)
+    for (int j = a.launched; j < a.launched + a.launches; ++j)
       hipLaunchKernelGGL(cand_step_kernel, dim3((unsigned)c.segs), dim3(kCandStepThreads), 0, s, c, cand_most(a), j, k,
                          a.best);
     return;

@@ -262,11 +262,13 @@ struct GreedyArgs {
   int k;               // greedy steps of the whole run, or 0 where they are launched one by one
   int all_nodes;       // nonzero: no candidate greedy (it left key 1 on this collection)
   int launched;        // launches of the candidate greedy before this call of launch_greedy
+  int launches;        // and in it
 };
-// Launches of the candidate greedy per call of launch_greedy.  Each takes one or
-// more of its k steps: 4 to 7 launches took k = 10, 6 to 10 k = 25, 13 to 16 k = 50.
-// One that finds all taken costs 4 us, a second call with its readback about 30 us.
-constexpr int cand_launches(int k) { return k / 4 + 5 < k ? k / 4 + 5 : k; }
+// Launches of the candidate greedy in the first call of launch_greedy.  Each takes
+// one or more of its k steps: 4 to 7 launches took k = 10, 6 to 10 k = 25, 13 to 18
+// k = 50.  One that finds all taken costs 2 to 4 us, a second call with its readback
+// about 30 us.
+constexpr int cand_launches(int k) { return 13 * k / 50 + 5 < k ? 13 * k / 50 + 5 : k; }
 // Workspace of the counting sort by node range that launch_counts and
 // launch_index use when GreedyArgs.bkt is set, and (index) of the candidate
 // greedy; 0 where they do not apply.
@@ -275,8 +277,8 @@ size_t bucket_workspace_bytes(int64_t n, uint64_t total, bool index);
 void launch_counts(const GreedyArgs& a, hipStream_t s);
 // With bkt and k set, launch_index and launch_greedy run the greedy over the
 // candidates of the largest counts where it applies.  launch_greedy then makes
-// cand_launches(k) launches, and while key k-1 is 0 (no choice's key is) it is
-// called again with `launched` advanced by as many.  Key 1 marks a step that the
+// `launches` launches, and while key k-1 is 0 (no choice's key is) it is called
+// again with `launched` advanced by as many.  Key 1 marks a step that the
 // candidates do not decide: both are launched again with all_nodes set.
 void launch_index(const GreedyArgs& a, hipStream_t s);
 void launch_greedy(const GreedyArgs& a, int k, hipStream_t s);

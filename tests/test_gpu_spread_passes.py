@@ -10,7 +10,7 @@ import oracle
 import synth
 
 pytestmark = pytest.mark.gpu
-IC, LT = 0, 1
+IC, LT, TRIGGER = 0, 1, 2
 
 
 @pytest.fixture(scope="module")
@@ -69,4 +69,19 @@ def test_mixed_runs_equal_oracle(eng, n, model):
         want = oracle.forward_spread(g, model, 11, (1 << 32) - 50, runs, seeds)
         assert np.array_equal(per.cpu().numpy().astype(np.int64), np.asarray(want, dtype=np.int64))
         assert total == int(np.sum(want))
+    eng.free(dg)
+
+
+def test_triggering_runs_equal_oracle(eng):
+    n = 262_145
+    g = synth.chung_lu(n, 3 * n, 2.1, 5)
+    trig = synth.random_triggering(g, 6)
+    dg = eng.upload(g)
+    eng.set_triggering(dg, g, trig)
+    hub = int(np.argsort(-np.bincount(g.src, minlength=n))[200])
+    for seeds in ([hub], [5, 77, hub]):
+        print(f"triggering seeds={seeds}", file=sys.stderr, flush=True)
+        _, total, per = eng.spread(dg, TRIGGER, 11, seeds, 1500, per_run=True)
+        want = oracle.forward_spread(g, TRIGGER, 11, 0, 1500, seeds, thr=trig)
+        assert np.array_equal(per.cpu().numpy().astype(np.int64), np.asarray(want, dtype=np.int64))
     eng.free(dg)
