@@ -2022,15 +2022,15 @@ constexpr int kChainWaves = 4;  // wavefronts per block of the long-chain tier
 // as long as one of them.  A launch of at most kLtHashMost such chains therefore
 // walks them once, marking the nodes in an LDS table per lane, with few chains
 // per wavefront; a chain of kLtHashCap nodes goes on with the search from there
-// (20000 widths on cycles of 250 nodes: 1.10 ms by the search alone, 1.19 so, 1.33
+// (20000 widths on cycles of 250 nodes: 1.10 ms by the search alone, 1.14 so, 1.33
 // with a search that starts at the root again; on random chains of 690 nodes, 404
-// widths: 9.2 and 6.2 ms).  With 64 KB
+// widths 9.2 and 6.3 ms, 20000 widths 12.6 and 12.9).  With 64 KB
 // of tables per wavefront only two fit a CU: longer lists keep to the search,
 // which fills the chip.  LT with in-weights on the 1M-node graph: 753 to 885 us
 // per launch by the search, 160 us with tables (TIM+ with k = 10: 8.2 -> 5.7 ms).
 constexpr int kLtHashLog = 8;
 constexpr uint32_t kLtHashCap = 192;
-constexpr uint32_t kLtHashSave = 128;  // the largest power of two below: the search's tortoise stands at node 127 then
+constexpr uint32_t kLtHashPower = 256;  // steps the search then takes before the tortoise moves up
 constexpr int kLtHashBlocks = 512;  // one wavefront each, two per CU
 constexpr unsigned long long kLtHashMost = (unsigned long long)kLtHashBlocks * kWave;
 
@@ -2113,14 +2113,13 @@ __device__ __forceinline__ void lt_chain_run(const SampleArgs& a, const TierIO& 
             acc.covered += 1;
             done = true;
           } else if (len == kLtHashCap) {
-            // these are distinct: the search goes on from where it would be after as many steps
+            // these are distinct: the search goes on with the last of them as the tortoise
             phase = kSearch;
             pos = kLtHashCap - 1;
-            power = kLtHashSave;
-            lam = kLtHashCap - kLtHashSave;
-            width = 0;
-          } else if (len == kLtHashSave) {
             tort = nx;
+            power = kLtHashPower;
+            lam = 0;
+            width = 0;
           }
         } else if (MODE != kModeEmit) {
           done = true;
