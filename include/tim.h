@@ -228,8 +228,8 @@ typedef struct {
   uint64_t index_calls;             /* greedy runs with the counts and index they work on; one whose candidates do not
                                        decide every step runs again over all nodes and counts twice */
   double index_ms, greedy_ms;
-  tim_kernel_profile ic_wide[3];    /* IC launches of few sets (fewer than n / 20 and 262144; with 8 edges per
-                                       node or more fewer than 65536 at least), which run the 64-lane first
+  tim_kernel_profile ic_wide[3];    /* IC launches of few sets (fewer than n / 20 and 262144, or than 2048, or
+                                       with 10 edges per node or more than 65536), which run the 64-lane first
                                        tier; sampler[0][] holds the others */
   tim_kernel_profile grouped[2];    /* [model] multi-job launches that run several early KptEstimation rounds
                                        at once, one job per round; sets counts every set they sampled,

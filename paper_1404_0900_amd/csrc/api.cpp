@@ -372,23 +372,26 @@ void hub_submit(Hub* h, Pending* p) {
 // kWideLaunchSets (width launches of 3000, 30000 and 100000 sets on 15K nodes
 // with 4 edges each took 125, 206, 272 us with 64 lanes and 108, 161, 199 with
 // the default; 8000, 60000, 200000 sets on 150K nodes 169, 260, 363 and 97, 185,
-// 214).
-// More edges: at least kWideDense sets (15K nodes with 16 edges each, 3000,
-// 30000, 100000 sets: 177, 244, 407 and 308, 355, 411; with 50 edges, 30000 and
-// 120000 sets: 624, 939 and 768, 940; 1M nodes with 10, 40000, 60000, 200000 sets:
-// 426, 483, 747 and 428, 465, 561).
+// 214), but at least kWideFew (over 12 graphs each of 1K, 3K, 8K and 30K nodes,
+// 1000 sets take 5 to 17% longer with the default, 2000 sets between 9% less and
+// 5% more, 4000 sets 6 to 28% less).
+// More edges: at least kWideDense sets (15K nodes with 12 edges each, 3000, 30000,
+// 100000 sets: 134, 219, 392 and 160, 287, 389; with 50 edges, 30000 and 120000
+// sets: 624, 939 and 768, 940; 1M nodes with 10, 40000, 60000, 200000 sets: 426,
+// 483, 747 and 428, 465, 561).
 // Stored sets take it too, with the node-pool bound of that shape (tier0_cap),
 // except in the chunked collections, which plan their pool for the context's
 // shape.  Batched launches keep theirs.
 constexpr uint64_t kWideLaunchSets = 262144;
 constexpr uint64_t kWideNodes = 20;
-constexpr int64_t kWideDegree = 8;
+constexpr uint64_t kWideFew = 2048;
+constexpr int64_t kWideDegree = 10;
 constexpr uint64_t kWideDense = 65536;
 
 // Lanes per set of the IC first tier for a launch of `count` sets on graph g.
 int launch_lanes(const tim_ctx* c, const tim_graph* g, int model, int mode, uint64_t count) {
-  uint64_t few = std::min<uint64_t>(kWideLaunchSets, (uint64_t)g->n / kWideNodes);
-  if (g->m >= kWideDegree * g->n) few = std::max(few, kWideDense);
+  const uint64_t least = g->m >= kWideDegree * g->n ? kWideDense : kWideFew;
+  const uint64_t few = std::max(least, std::min(kWideLaunchSets, (uint64_t)g->n / kWideNodes));
   if (c->wide_small && !c->hub && model == TIM_MODEL_IC && count < few &&
       (mode != tim::kModeEmit || c->emit_wave_sets == 0))
     return 64;

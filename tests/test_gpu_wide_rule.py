@@ -1,6 +1,6 @@
 """Which first-tier shape an IC launch of few sets takes (by the profile's ic_wide entries): below one set per twenty nodes
-the 64-lane shape on sparse graphs, below 65536 sets on graphs of eight edges per node or more.  Widths, sizes and the kappa
-sum equal the oracle's on both sides of the line."""
+or 2048 sets the 64-lane shape on sparse graphs, below 65536 sets on graphs of ten edges per node or more.  Widths, sizes and
+the kappa sum equal the oracle's on both sides of the line."""
 import sys
 
 import numpy as np
@@ -13,8 +13,9 @@ pytestmark = pytest.mark.gpu
 IC = 0
 
 
-@pytest.mark.parametrize("n,m,line", [(3000, 12000, 150), (40001, 160004, 2000), (3000, 23999, 150), (3000, 24000, 65536),
-                                      (1_400_000, 11_300_000, 70000)])
+@pytest.mark.parametrize("n,m,line", [(3000, 12000, 2048), (40001, 160004, 2048), (100001, 400004, 5000),
+                                      (3000, 29999, 2048), (3000, 30000, 65536),
+                                      (1_400_000, 14_000_000, 70000)])
 def test_lines_between_the_shapes(n, m, line):
     import paper_1404_0900_amd as tim
     g = synth.chung_lu(n, m, 2.1, 3)
