@@ -70,11 +70,11 @@ MODES = ("widths", "store", "cover")
 # WRITE_SIZE runs of this benchmark (scaled by a plain-copy calibration; see
 # profiles/ic_seg_kernel_chunglu_n1e6_m1e7.md), for the shapes the autotuner
 # picks on this graph.  Valid only for the kernel sources they were taken on.
-TRAFFIC = {  # by shape (kernel_name); both are ic_pool_kernel's
+TRAFFIC = {  # by shape (kernel_name): the default one's two modes, which ic_pool_kernel runs
     "ic_seg_kernel<1, true, 8, 128, 0, 512, 1> (store)": {
-        "sources_sha256_16": "f6456fde9b9b0942", "taken": "2026-12-05", "fetch_bytes": 2021886916, "write_bytes": 333056997},
+        "sources_sha256_16": "f2c2b35ac6e7b81f", "taken": "2026-12-05", "fetch_bytes": 2022395212, "write_bytes": 333055253},
     "ic_seg_kernel<0, true, 8, 128, 0, 512, 1> (widths)": {
-        "sources_sha256_16": "f6456fde9b9b0942", "taken": "2026-12-05", "fetch_bytes": 2728046249, "write_bytes": 91489653},
+        "sources_sha256_16": "f2c2b35ac6e7b81f", "taken": "2026-12-05", "fetch_bytes": 2728320611, "write_bytes": 91464395},
 }
 KERNEL_SOURCES = ("paper_1404_0900_amd/csrc/sample.hip", "paper_1404_0900_amd/csrc/rng.hpp",
                   "paper_1404_0900_amd/csrc/pick.hpp", "paper_1404_0900_amd/csrc/engine.hpp")
